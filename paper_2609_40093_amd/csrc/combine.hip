@@ -8,14 +8,18 @@
 // from +0, then one round-to-nearest-even conversion to bf16 (v_cvt_pk_bf16_f32), or the
 // fp32 accumulator itself.  HBM-bound: k row reads and one row write per token.
 //
-// Mapping: one wave per (token, column chunk of 64*U 16-byte vectors); the k slot
-// positions and gates are wave-uniform scalar loads.  Slots are taken KC at a time and
-// all KC*U row loads of a batch are issued before their FMAs, keeping KC*U KiB in flight
-// per wave.  Nothing is conditional: a slot without a row reads row 0 with its bits
-// masked to +0 and its gate set to -0, so it adds exactly -0, which leaves every sum
-// unchanged (signs of zero included) -- a branch around it would let the compiler sink
-// the slot's loads into the branch and serialize them behind the previous slot's.  In
-// EXACT instances (rows a whole number of chunks) no lane carries a bounds mask either.
+// Mapping: one wave per (token, column chunk); the k slot positions and gates are
+// wave-uniform scalar loads.  Slots are taken KC at a time (all k at once up to 8).  Where
+// every slot of a batch has a row, all KC*U row loads are issued before the FMAs and
+// nothing is conditional.  Otherwise (a window layout: most slots name other ranks'
+// experts) only the rows that exist are read, in slot order, up to four at a time; a slot
+// without a row adds nothing.  Reading row 0 for such slots instead, with its bits masked,
+// took 19.7 us at 2048 gathered tokens of 14 KiB rows with one slot of 8 in the window
+// (this: 10.5 us, 5.6 TB/s) and 155 us at 65536 tokens of 4 KiB rows (85 us, 6.3 TB/s).
+// A lane loads what makes one 16-byte vector of the output, so the stores of a wave are
+// contiguous also for fp32 results (16-byte loads and two stores 32 bytes apart per lane:
+// 31.5 us at 2047 tokens, top-4 of 10 KiB rows to fp32; this: 19.6 us, 6.4 TB/s).
+// In EXACT instances (rows a whole number of chunks) no lane carries a bounds mask.
 // Rows are read once: loads are non-temporal.  Stores are device-scope write-through
 // buffer stores when the output is under 128 MiB and non-temporal from there up (RowStore),
 // where the call runs as launches of about 64 MiB of output each (see the launcher):
@@ -39,101 +43,148 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, b);
 }
 
+// What one lane moves of a row per load: enough input elements for one 16-byte vector of
+// the output (8 bf16, or 4 bf16 widened to fp32), so that a wave's stores are contiguous
+// kilobytes for both output types.
+template <bool F32_OUT>
+struct Unit {
+    typedef u32x4 In;
+    static constexpr int kWords = 4;
+};
+template <>
+struct Unit<true> {
+    typedef uint32_t In __attribute__((ext_vector_type(2)));
+    static constexpr int kWords = 2;
+};
+
+// Adds N rows (the slots of the N lowest bits of `slots`, which are cleared) to acc, in
+// slot order, every load of the N rows issued before the first FMA.
+template <int N, int U, bool F32_OUT, bool EXACT>
+__device__ __forceinline__ void add_slots(float (&acc)[U][2 * Unit<F32_OUT>::kWords],
+                                          const typename Unit<F32_OUT>::In *recv, const int32_t *sp, const float *wt,
+                                          uint32_t &slots, int32_t v0, int lane, int32_t V) {
+    constexpr int kW = Unit<F32_OUT>::kWords;
+    typename Unit<F32_OUT>::In d[N][U];
+    float g[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int j = __builtin_ctz(slots);
+        slots &= slots - 1;
+        const typename Unit<F32_OUT>::In *src = recv + (int64_t)sp[j] * V;
+        g[i] = wt[j];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t v = v0 + u * kWave + lane;
+            d[i][u] = __builtin_nontemporal_load(src + (EXACT ? v : min(v, V - 1)));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < kW; ++q) {
+                acc[u][2 * q] = __builtin_fmaf(g[i], bf16_lo(d[i][u][q]), acc[u][2 * q]);
+                acc[u][2 * q + 1] = __builtin_fmaf(g[i], bf16_hi(d[i][u][q]), acc[u][2 * q + 1]);
+            }
+}
+
 // FIXED_K: k == KC (one batch of slots, its bounds known at compile time).  SEL: the
 // receive buffer is chosen by a round counter in device memory (graph-replayed rounds);
-// without it the kernel loads nothing before the slot positions.
+// without it the kernel loads nothing before the slot positions.  V: units per row.
 template <int U, int KC, bool F32_OUT, bool EXACT, bool FIXED_K, bool SEL, bool WT>
-__global__ __launch_bounds__(256) void combine_kernel(const u32x4 *__restrict__ recv,
+__global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ recv_rows,
                                                       const int32_t *__restrict__ slot_pos,
-                                                      const float *__restrict__ topk_w, int64_t T,
-                                                      int32_t V, int32_t chunks, int32_t k,
+                                                      const float *__restrict__ topk_w, uint32_t T,
+                                                      int32_t V, FastDiv chunks, int32_t k,
                                                       void *__restrict__ out, int64_t max_rows,
                                                       RoundSel sel) {
+    typedef typename Unit<F32_OUT>::In In;
+    constexpr int kW = Unit<F32_OUT>::kWords;
     const int lane = threadIdx.x & (kWave - 1);
     if (SEL && (__hip_atomic_load(sel.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-        recv = static_cast<const u32x4 *>(sel.alt);
+        recv_rows = sel.alt;
+    const In *recv = static_cast<const In *>(recv_rows);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t item = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
-    const int64_t t = item / chunks;
+    const uint32_t item = blockIdx.x * (blockDim.x / kWave) + wave;
+    const uint32_t t = chunks.div(item);
     if (t >= T)
         return;
-    const int32_t v0 = (int32_t)(item - t * chunks) * (U * kWave);
+    const int32_t v0 = (int32_t)(item - t * chunks.d) * (U * kWave);
     const int32_t kk = FIXED_K ? KC : k;
-    const int32_t *sp = slot_pos + t * kk;
-    const float *wt = topk_w + t * kk;
 
-    float acc[U][8];
+    float acc[U][2 * kW];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
+        for (int q = 0; q < 2 * kW; ++q)
             acc[u][q] = 0.0f;
 
     for (int32_t j0 = 0; j0 < kk; j0 += KC) {
-        u32x4 d[KC][U];
-        float g[KC];
-        uint32_t keep[KC];  // all ones for a slot with a row, else 0
-        bool ok[KC];
-        // positions first, then every row load, then the gates (needed only by the FMAs);
-        // every load is issued for every jj (a slot past k has no row)
+        const int32_t *sp = slot_pos + (int64_t)t * kk + j0;  // wave-uniform: scalar loads
+        const float *wt = topk_w + (int64_t)t * kk + j0;
+        int32_t p[KC];
+        uint32_t slots = 0;  // the batch's slots that have a row
 #pragma unroll
-        for (int jj = 0; jj < KC; ++jj) {
-            const int32_t j = j0 + jj;
-            const int64_t p = j < kk ? (int64_t)sp[min(j, kk - 1)] : -1;  // wave-uniform
-            ok[jj] = p >= 0 && p < max_rows;
-            keep[jj] = ok[jj] ? ~0u : 0u;
-            const u32x4 *src = recv + (ok[jj] ? p : 0) * V;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t v = v0 + u * kWave + lane;
-                d[jj][u] = EXACT ? __builtin_nontemporal_load(src + v)
-                                 : __builtin_nontemporal_load(src + min(v, V - 1));
-            }
+        for (int j = 0; j < KC; ++j) {
+            p[j] = FIXED_K || j0 + j < kk ? sp[FIXED_K ? j : min(j, kk - j0 - 1)] : -1;
+            slots |= p[j] >= 0 && p[j] < max_rows ? 1u << j : 0u;
         }
+        if (slots == (1u << KC) - 1u) {
+            // every slot has a row: all loads, then the gates (needed only by the FMAs)
+            In d[KC][U];
+            float g[KC];
 #pragma unroll
-        for (int jj = 0; jj < KC; ++jj) {
-            const float gj = wt[min(j0 + jj, kk - 1)];
-            g[jj] = ok[jj] ? gj : -0.0f;
-        }
+            for (int j = 0; j < KC; ++j) {
+                const In *src = recv + (int64_t)p[j] * V;
 #pragma unroll
-        for (int jj = 0; jj < KC; ++jj)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t bits = d[jj][u][q] & keep[jj];
-                    acc[u][2 * q] = __builtin_fmaf(g[jj], bf16_lo(bits), acc[u][2 * q]);
-                    acc[u][2 * q + 1] = __builtin_fmaf(g[jj], bf16_hi(bits), acc[u][2 * q + 1]);
+                for (int u = 0; u < U; ++u) {
+                    const int32_t v = v0 + u * kWave + lane;
+                    d[j][u] = __builtin_nontemporal_load(src + (EXACT ? v : min(v, V - 1)));
                 }
+            }
+#pragma unroll
+            for (int j = 0; j < KC; ++j)
+                g[j] = wt[j];
+#pragma unroll
+            for (int j = 0; j < KC; ++j)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int q = 0; q < kW; ++q) {
+                        acc[u][2 * q] = __builtin_fmaf(g[j], bf16_lo(d[j][u][q]), acc[u][2 * q]);
+                        acc[u][2 * q + 1] = __builtin_fmaf(g[j], bf16_hi(d[j][u][q]), acc[u][2 * q + 1]);
+                    }
+            continue;
+        }
+        // only the slots with a row, in slot order, up to four at a time (the count is
+        // wave-uniform, so each step's loads are all in flight together)
+        while (KC > 4 && __builtin_popcount(slots) >= 4)
+            add_slots<4, U, F32_OUT, EXACT>(acc, recv, sp, wt, slots, v0, lane, V);
+        switch (__builtin_popcount(slots)) {
+        case 3: add_slots<3, U, F32_OUT, EXACT>(acc, recv, sp, wt, slots, v0, lane, V); break;
+        case 2: add_slots<2, U, F32_OUT, EXACT>(acc, recv, sp, wt, slots, v0, lane, V); break;
+        case 1: add_slots<1, U, F32_OUT, EXACT>(acc, recv, sp, wt, slots, v0, lane, V); break;
+        default: break;
+        }
     }
 
-    // the token's output row: V 16-byte vectors (bf16) or 2V (fp32)
-    constexpr int kVecs = F32_OUT ? 2 : 1;
-    const RowStore<WT ? kStoreWT : kStoreNT> dst((u32x4 *)out + t * V * kVecs, (uint32_t)V * kVecs * 16u);
+    // the token's output row: V 16-byte vectors
+    const RowStore<WT ? kStoreWT : kStoreNT> dst((u32x4 *)out + (int64_t)t * V, (uint32_t)V * 16u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int32_t v = v0 + u * kWave + lane;
         if (!EXACT && v >= V)
             continue;
-        if constexpr (F32_OUT) {
-            const u32x4 a = {__float_as_uint(acc[u][0]), __float_as_uint(acc[u][1]),
-                             __float_as_uint(acc[u][2]), __float_as_uint(acc[u][3])};
-            const u32x4 b = {__float_as_uint(acc[u][4]), __float_as_uint(acc[u][5]),
-                             __float_as_uint(acc[u][6]), __float_as_uint(acc[u][7])};
-            dst.put(a, 2u * (uint32_t)v);
-            dst.put(b, 2u * (uint32_t)v + 1u);
-        } else {
-            const u32x4 r = {pack_bf16x2(acc[u][0], acc[u][1]), pack_bf16x2(acc[u][2], acc[u][3]),
-                             pack_bf16x2(acc[u][4], acc[u][5]), pack_bf16x2(acc[u][6], acc[u][7])};
-            dst.put(r, (uint32_t)v);
-        }
+        u32x4 r;
+        if constexpr (F32_OUT)
+            r = u32x4{__float_as_uint(acc[u][0]), __float_as_uint(acc[u][1]), __float_as_uint(acc[u][2]),
+                      __float_as_uint(acc[u][3])};
+        else
+            r = u32x4{pack_bf16x2(acc[u][0], acc[u][1]), pack_bf16x2(acc[u][2], acc[u][3]),
+                      pack_bf16x2(acc[u][4], acc[u][5]), pack_bf16x2(acc[u][6], acc[u][7])};
+        dst.put(r, (uint32_t)v);
     }
-}
-
-// With no rows to read every output is zero (each sum is empty).
-__global__ __launch_bounds__(256) void zero_fill_kernel(u32x4 *__restrict__ out, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        out[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
 constexpr int64_t kCombineWriteThroughBelow = 128ll << 20;  // output bytes
@@ -146,72 +197,83 @@ constexpr int64_t kCombineWriteThroughBelow = 128ll << 20;  // output bytes
 constexpr int64_t kCombineSplitAbove = 128ll << 20;
 constexpr int64_t kCombineLaunchBytes = 64ll << 20;
 
-template <int U, int KC, bool WT>
-void launch_ukw(dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts, const u32x4 *rv, const int32_t *slot_pos,
-                const float *topk_w, int64_t T, int32_t V, int32_t chunks, int32_t k, void *out, bool out_f32,
-                bool exact, int64_t max_rows, RoundSel sel) {
-#define EP_COMBINE_ARGS grid, block, 0, stream, ts.start, ts.stop, 0, rv, slot_pos, topk_w, T, V, chunks, k, out, max_rows, sel
-#define EP_COMBINE_LAUNCH(F32, EX)                                                                      \
-    (k == KC ? hipExtLaunchKernelGGL((combine_kernel<U, KC, F32, EX, true, false, WT>), EP_COMBINE_ARGS) \
-             : hipExtLaunchKernelGGL((combine_kernel<U, KC, F32, EX, false, false, WT>), EP_COMBINE_ARGS))
-    if (sel.round && out_f32)  // graph-replayed rounds: the general instance reading the round
-        hipExtLaunchKernelGGL((combine_kernel<U, KC, true, false, false, true, WT>), EP_COMBINE_ARGS);
-    else if (sel.round)
-        hipExtLaunchKernelGGL((combine_kernel<U, KC, false, false, false, true, WT>), EP_COMBINE_ARGS);
-    else if (out_f32 && exact)
-        EP_COMBINE_LAUNCH(true, true);
-    else if (out_f32)
-        EP_COMBINE_LAUNCH(true, false);
-    else if (exact)
-        EP_COMBINE_LAUNCH(false, true);
-    else
-        EP_COMBINE_LAUNCH(false, false);
-#undef EP_COMBINE_LAUNCH
-#undef EP_COMBINE_ARGS
-}
+struct CombineCall {
+    const void *recv;
+    const int32_t *slot_pos;
+    const float *topk_w;
+    int64_t T;
+    int32_t V, k;  // V: units (16-byte output vectors) per row
+    void *out;
+    int64_t max_rows;
+    RoundSel sel;
+};
 
-template <int U, int KC>
-hipError_t launch_uk(const void *recv, const int32_t *slot_pos, const float *topk_w, int64_t T,
-                     int32_t V, int32_t k, void *out, bool out_f32, int64_t max_rows,
-                     hipStream_t stream, RoundSel sel) {
-    const int32_t chunks = (V + U * kWave - 1) / (U * kWave);
-    const int waves_per_block = 4;
-    const int64_t row_bytes = (int64_t)V * 16 * (out_f32 ? 2 : 1);  // one output row
-    const int64_t out_bytes = T * row_bytes;
-    // token ranges of the launches: one below kCombineSplitAbove bytes of output, else
-    // about kCombineLaunchBytes each
-    const int64_t launches = out_bytes < kCombineSplitAbove
+// Launches one call as its token ranges.
+template <int U, int KC, bool F32_OUT, bool EXACT, bool FIXED_K, bool SEL>
+hipError_t launch_ranges(const CombineCall &c, hipStream_t stream) {
+    constexpr int kWaves = 4;  // per workgroup
+    const FastDiv chunks = fast_div((uint32_t)((c.V + U * kWave - 1) / (U * kWave)));
+    const int64_t row_bytes = (int64_t)c.V * 16;
+    const int64_t out_bytes = c.T * row_bytes;
+    // token ranges of the launches: one below kCombineSplitAbove bytes of output or with
+    // few rows to read, else about kCombineLaunchBytes each; never more items than FastDiv
+    // divides
+    const bool few_rows = c.max_rows <= c.T * c.k / 2;
+    const int64_t launches = out_bytes < kCombineSplitAbove || few_rows
                                  ? 1
-                                 : std::min<int64_t>(T, (out_bytes + kCombineLaunchBytes - 1) / kCombineLaunchBytes);
-    const int64_t per = (T + launches - 1) / launches;
-    if ((per * chunks + waves_per_block - 1) / waves_per_block > INT32_MAX)
+                                 : std::min<int64_t>(c.T, (out_bytes + kCombineLaunchBytes - 1) / kCombineLaunchBytes);
+    const int64_t per = std::min<int64_t>((c.T + launches - 1) / launches, (INT32_MAX - kWaves) / chunks.d);
+    if (per < 1)
         return hipErrorInvalidValue;
-    const bool exact = V % (U * kWave) == 0;
-    const dim3 block(waves_per_block * kWave);
-    const u32x4 *rv = static_cast<const u32x4 *>(recv);
+    const bool wt = out_bytes < kCombineWriteThroughBelow;
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
     const TraceSlot ts = trace_acquire();  // one pair of events around every launch of the call
-    const bool wt = out_bytes < kCombineWriteThroughBelow;
-    for (int64_t t0 = 0; t0 < T; t0 += per) {
-        const int64_t n = std::min(per, T - t0);
-        const dim3 grid((unsigned)((n * chunks + waves_per_block - 1) / waves_per_block));
-        TraceSlot part;
-        part.start = t0 == 0 ? ts.start : nullptr;
-        part.stop = t0 + n == T ? ts.stop : nullptr;
-        const int32_t *sp = slot_pos + t0 * k;
-        const float *gw = topk_w + t0 * k;
-        void *o = static_cast<char *>(out) + t0 * row_bytes;
-        if (wt)
-            launch_ukw<U, KC, true>(grid, block, stream, part, rv, sp, gw, n, V, chunks, k, o, out_f32, exact,
-                                    max_rows, sel);
-        else
-            launch_ukw<U, KC, false>(grid, block, stream, part, rv, sp, gw, n, V, chunks, k, o, out_f32, exact,
-                                     max_rows, sel);
+    for (int64_t t0 = 0; t0 < c.T; t0 += per) {
+        const int64_t n = std::min(per, c.T - t0);
+        const dim3 grid((unsigned)((n * chunks.d + kWaves - 1) / kWaves)), block(kWaves * kWave);
+        const hipEvent_t start = t0 == 0 ? ts.start : nullptr, stop = t0 + n == c.T ? ts.stop : nullptr;
+        auto go = [&](auto kern) {
+            hipExtLaunchKernelGGL(kern, grid, block, 0, stream, start, stop, 0, c.recv, c.slot_pos + t0 * c.k,
+                                  c.topk_w + t0 * c.k, (uint32_t)n, c.V, chunks, c.k,
+                                  static_cast<void *>(static_cast<char *>(c.out) + t0 * row_bytes), c.max_rows, c.sel);
+        };
+        wt ? go(combine_kernel<U, KC, F32_OUT, EXACT, FIXED_K, SEL, true>)
+           : go(combine_kernel<U, KC, F32_OUT, EXACT, FIXED_K, SEL, false>);
     }
-    hipError_t err = hipGetLastError();
+    const hipError_t err = hipGetLastError();
     if (err == hipSuccess)
         trace_submit("combine", ts);
     return err;
+}
+
+// Picks the instance for batches of KC slots.  U units per lane for bf16 results, 2U for
+// fp32 results, whose units hold half as many elements of a row.
+template <int U, int KC, bool FIXED_K>
+hipError_t launch_u(const CombineCall &c, bool out_f32, bool exact, hipStream_t stream) {
+    if (exact)
+        return out_f32 ? launch_ranges<2 * U, KC, true, true, FIXED_K, false>(c, stream)
+                       : launch_ranges<U, KC, false, true, FIXED_K, false>(c, stream);
+    if constexpr (U == 1)  // the others are only used for whole rows
+        return out_f32 ? launch_ranges<2, KC, true, false, FIXED_K, false>(c, stream)
+                       : launch_ranges<1, KC, false, false, FIXED_K, false>(c, stream);
+    return hipErrorInvalidValue;
+}
+
+// Chunk length, measured on MI355X (2000 tokens of 14 KiB rows, 4000 of 8 KiB, 9001 of
+// 4112 B; bf16 and fp32 results): two-unit chunks where they cover the row exactly, within
+// 1.5% of one-unit chunks or ahead of them for every k; one-unit chunks for other rows
+// (4112 B rows, fp32: top-4 36.4 against 37.8 us, top-8 65.7 against 69.7) and for k >= 8
+// with rows of at least 12 KiB (2% ahead at 32768 tokens); four for top-4 to bf16 where
+// they are exact (25.4 against 26.0 us).  A batch of exactly k slots (k <= 8) beats batches
+// of four and the rest (top-6, 4112 B rows: 43.4 against 44.9 us, fp32 53.9 against 61.8).
+template <int KC, bool FIXED_K>
+hipError_t launch_k(const CombineCall &c, int32_t H, bool out_f32, hipStream_t stream) {
+    if constexpr (KC == 4)
+        if (!out_f32 && H % 2048 == 0)
+            return launch_u<4, KC, FIXED_K>(c, out_f32, true, stream);
+    if (H % 1024 == 0 && !(KC == 8 && H >= 6144))
+        return launch_u<2, KC, FIXED_K>(c, out_f32, true, stream);
+    return launch_u<1, KC, FIXED_K>(c, out_f32, H % 512 == 0, stream);
 }
 
 // One pass of the per-sender accumulation (a combine that reduces each sender's returned
@@ -224,7 +286,7 @@ hipError_t launch_uk(const void *recv, const int32_t *slot_pos, const float *top
 // combine_kernel -- and writes a token whose prefix is complete to `out`.  Sets only
 // grow, so every slot is added once and in slot order: the result equals combine_kernel's
 // bit for bit whatever order the senders arrive in.  A slot without a row is skipped:
-// combine_kernel adds exactly -0 for it, which changes nothing.  One wave per (token,
+// combine_kernel skips it too.  One wave per (token,
 // 64-vector chunk).
 template <bool F32_OUT>
 __global__ __launch_bounds__(256) void accumulate_kernel(const u32x4 *__restrict__ recv,
@@ -329,28 +391,21 @@ hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float
                           int64_t max_rows, hipStream_t stream, RoundSel sel) {
     if (T == 0)
         return hipSuccess;
-    const int32_t V = H / 8;
-    if (max_rows <= 0) {  // the kernels below read row 0 for slots without a row
-        const int64_t n = T * V * (out_f32 ? 2 : 1);
-        const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
-        (void)hipGetLastError();
-        hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, static_cast<u32x4 *>(out), n);
-        return hipGetLastError();
+    const CombineCall c{recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
+    if (sel.round)  // graph-replayed rounds: the general instance reading the round
+        return out_f32 ? launch_ranges<4, 8, true, false, false, true>(c, stream)
+                       : launch_ranges<2, 8, false, false, false, true>(c, stream);
+    switch (k) {
+    case 1: return launch_k<1, true>(c, H, out_f32, stream);
+    case 2: return launch_k<2, true>(c, H, out_f32, stream);
+    case 3: return launch_k<3, true>(c, H, out_f32, stream);
+    case 4: return launch_k<4, true>(c, H, out_f32, stream);
+    case 5: return launch_k<5, true>(c, H, out_f32, stream);
+    case 6: return launch_k<6, true>(c, H, out_f32, stream);
+    case 7: return launch_k<7, true>(c, H, out_f32, stream);
+    case 8: return launch_k<8, true>(c, H, out_f32, stream);
+    default: return launch_k<8, false>(c, H, out_f32, stream);
     }
-    // KC*U 16-byte loads per lane in flight: 16 for k >= 4 (8 for k >= 8 with rows of at
-    // least 12 KiB), 4 for k = 2 and 3.  Measured on MI355X: at k = 8 and 14 KiB rows,
-    // one-group chunks (twice the waves) beat two-group chunks by 2% at 32768 tokens and
-    // 1% at 16384, and tie at a few thousand; with 4 KiB rows two-group chunks are ahead
-    // by 1%.  At k = 2, two-group chunks beat four-group ones.
-    if (k >= 8 && V >= 768)
-        return launch_uk<1, 8>(recv, slot_pos, topk_w, T, V, k, out, out_f32, max_rows, stream, sel);
-    if (k >= 8)
-        return launch_uk<2, 8>(recv, slot_pos, topk_w, T, V, k, out, out_f32, max_rows, stream, sel);
-    if (k >= 4)
-        return launch_uk<4, 4>(recv, slot_pos, topk_w, T, V, k, out, out_f32, max_rows, stream, sel);
-    if (k >= 2)
-        return launch_uk<2, 2>(recv, slot_pos, topk_w, T, V, k, out, out_f32, max_rows, stream, sel);
-    return launch_uk<4, 1>(recv, slot_pos, topk_w, T, V, k, out, out_f32, max_rows, stream, sel);
 }
 
 hipError_t launch_accumulate(const void *recv, const int32_t *slot_pos, const float *topk_w, int64_t T, int32_t H,

@@ -56,6 +56,20 @@ struct RowStore<kStoreNT> {
     __device__ __forceinline__ void put(u32x4 v, uint32_t vec) const { __builtin_nontemporal_store(v, base + vec); }
 };
 
+// Division of a wave-uniform 31-bit number by a number known at launch (multiply-high, add,
+// shift: Granlund and Montgomery, "Division by Invariant Integers using Multiplication", with
+// the add in 32 bits because n < 2^31).
+struct FastDiv {
+    uint32_t d, mul, shift;
+    __device__ __forceinline__ uint32_t div(uint32_t n) const { return (__umulhi(n, mul) + n) >> shift; }
+};
+inline FastDiv fast_div(uint32_t d) {  // 1 <= d < 2^31
+    uint32_t shift = 0;
+    while ((1ull << shift) < d)
+        ++shift;
+    return {d, (uint32_t)((((1ull << shift) - d) << 32) / d + 1), shift};
+}
+
 // ---- layout geometry -----------------------------------------------------------
 // The routing array is cut into tiles, one workgroup each; a workgroup has W waves and
 // each wave walks `rounds` rounds of 64 entries.  W = 16 while 16 rows of per-wave

@@ -1,0 +1,47 @@
+"""The combine with slots that have no row, over every batch length (k = 1..8 in one batch,
+9 and 16 in several), chunk length and row remainder, bf16 and fp32 results.
+
+Reference: the sum in float64 over the slots with a row.  The kernel does n fp32 FMAs from
++0 (n slots with a row), each with a relative rounding of 2^-24 of its result, and every
+partial sum is at most S = sum |w y| (1 + n 2^-24): the fp32 result is within n 2^-24 S
+(taken as (n + 1) 2^-24 S), a bf16 result within half a bf16 step more (a step is 2^-7 of
+the power of two below the value, so half a step is at most 2^-8 of the value).
+A token without any row is +0, bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_40093_amd as ep
+from gpu_cases import say
+from paper_2609_40093_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("H", [8, 512, 520, 1024, 2048, 3072, 6152, 7168])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 16])
+def test_slots_without_rows(k, H):
+    T, rows = 129, 97
+    rng = np.random.default_rng([k, H])
+    y = synth.normal_bf16_rows(np.random.SeedSequence([k, H]), rows, H)
+    w = rng.standard_normal((T, k)).astype(np.float32)
+    pos = rng.integers(0, rows, (T, k)).astype(np.int32)
+    # tokens with every slot, with about half and with few; -1 and rows past the last one
+    missing = rng.random((T, k)) < np.array([0.0, 0.5, 0.9])[np.arange(T) % 3][:, None]
+    pos[missing] = rng.choice(np.array([-1, rows, rows + 7, 2**31 - 1], np.int32), int(missing.sum()))
+    has = ~missing
+    yf = synth.bf16_bits_to_f32(y).astype(np.float64)
+    terms = np.where(has[:, :, None], w.astype(np.float64)[:, :, None] * yf[np.where(has, pos, 0)], 0.0)
+    exact, size = terms.sum(axis=1), np.abs(terms).sum(axis=1)
+    bound = (has.sum(axis=1)[:, None] + 1) * 2.0**-24 * size
+    say(f"combine_rows with missing slots: k={k} H={H}")
+    args = [torch.from_numpy(a).to(DEV) for a in (y.view(np.int16), pos.reshape(-1), w)]
+    for dt, extra in ((torch.float32, 0.0), (torch.bfloat16, 2.0**-8)):
+        out = torch.full((T, H), 7.0, dtype=dt, device=DEV)
+        ep.combine_rows(args[0], args[1], args[2], out)
+        got = out.double().cpu().numpy()
+        assert (np.abs(got - exact) <= bound + extra * (np.abs(exact) + bound)).all()
+        empty = ~has.any(axis=1)
+        assert not out.view(torch.int32 if dt == torch.float32 else torch.int16).cpu().numpy()[empty].any()
