@@ -213,7 +213,6 @@ LayoutArgs layout_args(const int32_t *topk_idx, int64_t T, int32_t k, int32_t E,
     a.nbits = E > 1 ? 32 - __builtin_clz((unsigned)(E - 1)) : 0;
     a.e_lo = 0;
     a.all_E = E;
-    a.all_nbits = a.nbits;
     a.expert_counts = expert_counts;
     a.expert_offsets = expert_offsets;
     a.rank_counts = rank_counts;
@@ -278,7 +277,6 @@ extern "C" ep_status ep_dispatch_layout_local(const int32_t *topk_idx, int64_t n
     a.nbits = L > 1 ? 32 - __builtin_clz((unsigned)(L - 1)) : 0;
     a.e_lo = e_lo;
     a.all_E = E;
-    a.all_nbits = E > 1 ? 32 - __builtin_clz((unsigned)(E - 1)) : 0;
     a.expert_counts = local_counts;
     a.expert_offsets = local_offsets;
     a.rank_counts = reinterpret_cast<int32_t *>(ws + ep::kWorkspaceScratch);      // [1], unused by callers

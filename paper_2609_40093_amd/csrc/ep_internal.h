@@ -71,13 +71,27 @@ inline FastDiv fast_div(uint32_t d) {  // 1 <= d < 2^31
 }
 
 // ---- layout geometry -----------------------------------------------------------
-// The routing array is cut into tiles, one workgroup each; a workgroup has W waves and
-// each wave walks `rounds` rounds of 64 entries.  W = 16 while 16 rows of per-wave
-// counters fit in LDS (E <= 512), else 4.  One tile when it covers every entry in at most
-// 4 rounds (W = 16) or 8 rounds (W = 4): one kernel then does the whole layout.  Otherwise
-// as many tiles as keep the tile counts at most 16K words (every workgroup of the rank
-// kernel reads them all) and at most 1024 tiles, with as few rounds as that allows.  No tile waits for another, so the tile count is not tied to the device.
+// One kernel lays out few entries.  Otherwise the routing array is cut into tiles, counted by
+// one workgroup each: tiles of W * 64 * rounds entries, W = 16 for E <= 512, else 4; as many
+// tiles as keep the tile counts at most 16K words (every workgroup of the rank kernel reads
+// them all) and at most 1024 tiles, with as few rounds as that allows.  (Up to 4 rounds of
+// W = 16 or 8 of W = 4 the geometry has one tile and the workspace no counts.)  No tile
+// waits for another, so the tile count is not tied to the device.
 constexpr int kMaxExperts = 2048;
+// Entries up to which one kernel does the whole layout, each workgroup histogramming every
+// entry (top-k of 1, 2, 4 or 8; one tile for other k, whose routing checks take longer).
+// Measured on MI355X, layouts back to back, one kernel against two: 8188 entries 5.2 / 7.8
+// us, 16384 entries 6.7 / 8.7, 32768 entries 10.9 / 8.4.
+constexpr int64_t kLayoutOneKernelIds = 20480;
+// Rank workgroups aimed at over all tiles (one per compute unit), of 4 waves, or 16 above
+// kLayoutWideRank entries where a tile still has several workgroups.  Each reads the whole
+// count table and histograms its tile up to its run, so more or smaller workgroups pay that
+// more often: 1M entries of 256 experts (64 tiles) with 256 / 512 workgroups of 16 waves
+// 17.6 / 23.6 us, with 512 / 1024 of 4 waves 20.0 / 33.3 us; fewer, larger ones put more of
+// the ranking on one compute unit: 65536 entries of 128 experts, 4 / 16 waves 8.6 / 10.0 us,
+// 524288 entries of 16 (512 tiles) 11.1 / 15.5 us.
+constexpr int64_t kLayoutRankGroups = 256;
+constexpr int64_t kLayoutWideRank = 131072;
 constexpr int kLayoutRankCache = 8;  // rounds whose ids and in-wave ranks stay in registers
 struct LayoutGeom {
     int waves;
@@ -132,10 +146,12 @@ void trace_host(const char *name, double ms);
 struct LayoutArgs {
     const int32_t *topk_idx;
     int64_t slots;  // T*k
-    // E: experts grouped (the window [e_lo, e_lo + E) of all_E experts); nbits covers E,
-    // all_nbits covers all_E (duplicate check over the raw ids when the window is narrower)
+    // E: experts grouped (the window [e_lo, e_lo + E) of all_E experts); nbits covers E
     int32_t k, E, R, nbits;
-    int32_t e_lo = 0, all_E = 0, all_nbits = 0;
+    int32_t e_lo = 0, all_E = 0;
+    // set by launch_layout: experts per rank, division by k, E and E/4
+    int32_t L = 0;
+    FastDiv k_div, e_div, e4_div;
     int32_t *expert_counts, *expert_offsets, *rank_counts, *rank_offsets;
     int32_t *slot_pos, *row_src;
     uint32_t *status;        // workspace byte 0
