@@ -21,12 +21,9 @@
 // 31.5 us at 2047 tokens, top-4 of 10 KiB rows to fp32; this: 19.6 us, 6.4 TB/s).
 // In EXACT instances (rows a whole number of chunks) no lane carries a bounds mask.
 // Rows are read once: loads are non-temporal.  Stores are device-scope write-through
-// buffer stores when the output is under 128 MiB and non-temporal from there up (RowStore),
-// where the call runs as launches of about 64 MiB of output each (see the launcher):
-// measured on MI355X with inputs outside the memory-side cache, write-through stores made
-// the combine 2-7% faster up to 112 MiB of output (top-8 of 14 KiB rows, 2K-8K tokens;
-// 4 KiB rows, 8K tokens; top-2 of 8 KiB rows, 4K tokens) and 0.5-2% slower from 128 MiB
-// up (top-2, 16K tokens of 8 KiB rows; 16K and 32K tokens of 14 KiB rows).
+// buffer stores when the output is under kCombineWriteThroughBelow and non-temporal from
+// there up (RowStore); from 128 MiB up the call runs as launches of about 64 MiB of output
+// each (see the launcher).
 #include "ep_internal.h"
 
 namespace ep {
@@ -187,7 +184,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ r
     }
 }
 
-constexpr int64_t kCombineWriteThroughBelow = 128ll << 20;  // output bytes
+// Output bytes below which stores write through.  Such stores make the combine itself 1-9%
+// faster at any size, but from about 44 MiB of output on the next pack pays for what they
+// leave behind.  Measured on MI355X over whole passes (layout, pack, combine; buffers
+// rotated past the memory-side cache), write-through / non-temporal: 27 MiB (top-8 of 14 KiB
+// rows) 95.3 / 97.2 us, 35 MiB (top-2 of 8 KiB rows) 41.3 / 43.0, 41 MiB (top-8 of 14 KiB) 143.5 /
+// 144.8, 42 MiB (top-2 of 8 KiB) 50.5 / 50.6, 47 MiB (top-8 of 14 KiB) 180 / 167.7, 50 MiB (top-2
+// of 8 KiB) 65.5 / 58.4, 57 MiB (top-8 of 14 KiB) 211 / 191 (the pack 112 / 92).
+constexpr int64_t kCombineWriteThroughBelow = 44ll << 20;
 // From 128 MiB of output up the combine runs as several launches over consecutive token
 // ranges of about 64 MiB of output each (measured on MI355X, top-8 of 14 KiB rows, 32K
 // tokens, non-temporal stores: one launch 747 us, 2 / 4 / 8 / 16 / 32 / 64 launches 733 /

@@ -18,21 +18,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWave = 64;
 
 // Stores of one row (a packed row of the dispatch, an output row of the combine) from a
-// wave-uniform base, under one of three policies that each kernel picks by the bytes a
-// launch writes (measured on MI355X, inputs rotated past the memory-side cache):
+// wave-uniform base, under one of three policies:
 //   kStoreNT:        non-temporal stores;
 //   kStoreWT:        16-byte buffer stores at device scope (sc1: written through the XCD's
 //                    L2 rather than held there dirty);
 //   kStoreWTStream:  the same with the non-temporal hint as well (sc1 nt).
-// The pack (rows of 4 and 14 KiB) stores with kStoreWTStream from 2 GiB per launch up,
-// where the non-temporal rate falls with the size of the stream: at the prefill pack
-// (3.76 GB written) 764 us against 772 us with kStoreWT and 778 us non-temporal;
-// non-temporal is up to 20% faster at 0.1-1 GiB.  The combine writes through with kStoreWT
-// below 128 MiB of output (there kStoreWTStream measured 5-8% slower); its thresholds are
-// beside it.  The buffer range of a buffer-store row is the `bytes` from `base` on: a store
-// past it is dropped by the hardware.
+// Which one each kernel uses, by the bytes a launch writes, stands beside its launcher with
+// the measurements.  The buffer range of a buffer-store row is the `bytes` from `base` on: a
+// store past it is dropped by the hardware.
 constexpr int kStoreNT = 0, kStoreWT = 1, kStoreWTStream = 2;
-constexpr int64_t kWriteThroughBytes = 2ll << 30;  // the pack's
 template <int POL>
 struct RowStore {
     static_assert(POL == kStoreWT || POL == kStoreWTStream, "buffer-store policies");

@@ -4,178 +4,182 @@
 // gathered into one contiguous segment per destination (Sec. 2.2 of the paper).  The
 // kernel is HBM-bound: it reads each token row once and writes it k times.
 //
-// Mapping: a row of V 16-byte vectors is G = ceil(V/64) groups of 64 (one vector per
-// lane); a wave moves one chunk of `gpc` groups (all its loads in flight together) of one
-// row.  Consecutive lanes touch consecutive 16-byte pieces of the row: every load and
-// store is a fully coalesced 1 KiB wave access.
-//   EXACT instances: V is a multiple of 64 and the chunk length U divides G, so every
-//     load and store is unconditional, at a compile-time offset;
-//   generic instances (rows whose length is not a multiple of 64 vectors, or G with no
-//     usable divisor): chunks of up to U groups; loads stay unconditional (a group past
-//     the chunk's end reloads the chunk's last group, a lane past the row's end reloads
-//     the row's last vector: L2 hits, no HBM traffic); stores are guarded.
-//
-// Which mapping is used follows bandwidth measured on MI355X with inputs outside the
-// memory-side cache:
-//   k < 4:  one wave per (token, chunk): the chunk is loaded once (non-temporal) and
-//           stored to the k rows;
-//   k >= 4: one wave per (token, chunk, slot), the k waves of a chunk adjacent: each wave
-//           writes a single destination row; the chunk's loads after the first come from
-//           L2 (cached loads), and each wave feeds one write stream instead of k;
-//   chunk:  the largest divisor of G of at most 16 groups (16 KiB): a whole row for rows
-//           up to 16 KiB; long exact chunks measured faster than 4-group chunks and than
-//           16-group chunks with guarded tails.  Rows with no divisor of at least 4 groups
-//           (G a prime above 16) use the generic 16-group instance.
-// Stores: non-temporal below 2 GiB written per launch, device-scope write-through buffer
-// stores with the non-temporal hint from 2 GiB up (RowStore: each policy is the faster one
-// at its sizes).  Rows carry
-// no reuse across workgroups, so the workgroup-to-XCD placement needs no remapping.
+// Mapping: a row of V 16-byte vectors is G groups of 64 (one vector per lane); a wave moves
+// one chunk of U groups (all its loads in flight together) of one (token, slot): a single
+// destination row.  Consecutive lanes touch consecutive 16-byte pieces: every load and store
+// is a fully coalesced 1 KiB wave access.  The k waves of a chunk sit in one workgroup (up
+// to 16): its loads after the first come from L2 (cached loads), and each wave feeds one
+// write stream instead of k (against one wave storing its chunk k times, MI355X, inputs
+// outside the memory-side cache: 3001 tokens, top-3 of 12 KiB rows 22.1 against 29.5 us, 6.7
+// TB/s; top-2 of 4112 B rows, 4001 tokens 9.3 against 10.7 us).
+// Rows that are no whole number of 128-byte lines: groups are counted from the line that
+// holds the destination row's start, so that only the row's first and last stores touch
+// partly filled lines, and only those lanes are masked (5003 tokens, top-6 of 5776 B rows:
+// 38.4 against 42.7 us with groups counted from the row's start, whose every store splits two
+// lines).
+// Chunk: the largest divisor of G of at most 16 groups (16 KiB): a whole row for rows up to
+// 16 KiB; long exact chunks measured faster than 4-group chunks and than 16-group chunks
+// with guarded tails.  Rows with no divisor of at least 4 groups (G a prime above 16) use
+// 16-group chunks whose last may be shorter.
+// Stores: see pack_policy.  Rows carry no reuse across workgroups, so the
+// workgroup-to-XCD placement needs no remapping.
 #include "ep_internal.h"
 
 namespace ep {
 namespace {
 
 struct PackGeom {
-    int32_t V;       // 16-byte vectors per row
-    int32_t G;       // groups of 64 vectors per row
-    int32_t gpc;     // groups per chunk (<= the kernel's U)
-    int32_t chunks;  // chunks per row
+    int32_t V;          // 16-byte vectors per row
+    int32_t gpc;        // groups per chunk (<= the kernel's U)
+    int32_t G;          // groups of 64 vectors per row
+    uint32_t lead_mask; // 7 where rows are no whole number of 128-byte lines, else 0
+    FastDiv chunks;     // chunks per row
+    FastDiv k;          // top-k
 };
 
-// Vector of the row that lane `lane` loads for group u of a generic chunk starting at
-// group g0 with ng groups: always inside the row.
-__device__ __forceinline__ int32_t load_index(int32_t g0, int u, int32_t ng, int lane, int32_t V) {
-    return min((g0 + min(u, ng - 1)) * kWave + lane, V - 1);
-}
+// How a row's groups meet its ends.
+enum Edge {
+    kWhole,    // rows are whole groups and chunks whole numbers of U groups
+    kPartial,  // chunks whole numbers of U groups; the row's first and last groups may be
+               // partly filled
+    kRagged,   // the last chunk may have fewer groups, too
+};
 
-// Whether the store of group u of a generic chunk is inside the chunk and the row.
-__device__ __forceinline__ bool store_ok(int32_t g0, int u, int32_t ng, int lane, int32_t V) {
-    return u < ng && (g0 + u) * kWave + lane < V;
-}
-
-// One wave per (token, chunk): the chunk is loaded once and stored to the k rows.
-template <int U, bool EXACT, int SP>
-__global__ __launch_bounds__(256) void pack_kernel(const u32x4 *__restrict__ x, int64_t T, PackGeom pg, int32_t k,
-                                                   const int32_t *__restrict__ slot_pos,
-                                                   u32x4 *__restrict__ packed, int64_t max_rows,
-                                                   uint32_t *epoch_word, uint32_t epoch, RoundSel sel,
-                                                   bool fence_system) {
-    const int lane = threadIdx.x & (kWave - 1);
-    if (epoch_word && blockIdx.x == 0 && threadIdx.x == 0)
-        *epoch_word = epoch;
-    if (sel.round && (__hip_atomic_load(sel.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-        packed = static_cast<u32x4 *>(const_cast<void *>(sel.alt));
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t item = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
-    const int64_t t = item / pg.chunks;
-    if (t >= T)
-        return;
-    const int32_t g0 = (int32_t)(item - t * pg.chunks) * pg.gpc;
-    const int32_t ng = EXACT ? U : min(pg.gpc, pg.G - g0);  // wave-uniform, >= 1
-    const u32x4 *src = x + t * pg.V;
-    u32x4 d[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        d[u] = __builtin_nontemporal_load(src + (EXACT ? (g0 + u) * kWave + lane : load_index(g0, u, ng, lane, pg.V)));
-    const int32_t *sp = slot_pos + t * k;
-    for (int32_t j = 0; j < k; ++j) {
-        const int64_t p = sp[j];
-        if (p < 0 || p >= max_rows)
-            continue;
-        const RowStore<SP> dst(packed + p * pg.V + g0 * kWave, (uint32_t)(pg.V - g0 * kWave) * 16u);
+// The chunk of U groups number `chunk` of a row, one 16-byte vector of each group per lane.
+// Groups are counted from `lead` vectors before the destination row's start, where a 128-byte
+// line starts, so that every store but the row's first and last covers whole lines.
+template <int U, int EDGE>
+struct Chunk {
+    const int32_t first, ng, V;  // first: this lane's vector of group 0 (negative before the row)
+    __device__ __forceinline__ Chunk(const PackGeom &pg, int32_t chunk, int lane, int32_t lead)
+        : first(chunk * pg.gpc * kWave + lane - (EDGE == kWhole ? 0 : lead)),
+          ng(EDGE == kRagged ? min(pg.gpc, pg.G - chunk * pg.gpc) : U), V(pg.V) {}
+    // whether group u may reach past the row's ends: in the first group, and in the last two
+    // (the row's end moves back by up to seven lanes with the lead)
+    static constexpr bool edge(int u) { return EDGE == kRagged || (EDGE == kPartial && (u == 0 || u >= U - 2)); }
+    // vector of the row that this lane loads for group u: always inside the row
+    __device__ __forceinline__ int32_t load_index(int u) const {
+        const int32_t v = first + (EDGE == kRagged ? min(u, ng - 1) : u) * kWave;
+        return edge(u) ? max(0, min(v, V - 1)) : v;
+    }
+    __device__ __forceinline__ bool store_ok(int u) const {
+        return !edge(u) || (u < ng && (uint32_t)(first + u * kWave) < (uint32_t)V);
+    }
+    template <class Store>
+    __device__ __forceinline__ void store(const u32x4 (&d)[U], u32x4 *row) const {
+        const Store dst(row, (uint32_t)V * 16u);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (EXACT || store_ok(g0, u, ng, lane, pg.V))
-                dst.put(d[u], u * kWave + lane);
+            if (store_ok(u))
+                dst.put(d[u], first + u * kWave);
     }
-    if (fence_system)
-        __threadfence_system();
-}
+};
+
+// The arrays are arguments of their own (restrict-qualified: the positions are then scalar
+// loads; as vector loads they cost the 32768-token, top-8 pack of 14 KiB rows 5%).
+struct PackArgs {
+    uint32_t T;  // tokens of this launch
+    int32_t k;
+    PackGeom geom;
+    int64_t max_rows;
+    uint32_t *epoch_word;
+    uint32_t epoch;
+    RoundSel sel;
+    bool fence_system;
+    // Before anything else: the round's epoch, and the buffer it selects.
+    __device__ __forceinline__ u32x4 *begin(u32x4 *packed) const {
+        if (epoch_word && blockIdx.x == 0 && threadIdx.x == 0)
+            *epoch_word = epoch;
+        if (sel.round && (__hip_atomic_load(sel.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
+            return static_cast<u32x4 *>(const_cast<void *>(sel.alt));
+        return packed;
+    }
+};
 
 // One wave per (token, chunk, slot), the k waves of a chunk adjacent: each wave writes a
-// single destination row.
-template <int U, bool EXACT, int SP>
-__global__ __launch_bounds__(1024) void pack_slot_kernel(const u32x4 *__restrict__ x, int64_t T, PackGeom pg, int32_t k,
-                                                        const int32_t *__restrict__ slot_pos,
-                                                        u32x4 *__restrict__ packed, int64_t max_rows,
-                                                        uint32_t *epoch_word, uint32_t epoch, RoundSel sel,
-                                                        bool fence_system) {
-    const int lane = threadIdx.x & (kWave - 1);
-    if (epoch_word && blockIdx.x == 0 && threadIdx.x == 0)
-        *epoch_word = epoch;
-    if (sel.round && (__hip_atomic_load(sel.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-        packed = static_cast<u32x4 *>(const_cast<void *>(sel.alt));
+// single destination row.  ONCE: k == 1, the row is read once (non-temporal loads).
+template <int U, int EDGE, int SP, bool ONCE>
+__global__ __launch_bounds__(1024) void pack_kernel(const u32x4 *__restrict__ x,
+                                                    const int32_t *__restrict__ slot_pos,
+                                                    u32x4 *__restrict__ packed_rows, PackArgs a) {
+    u32x4 *const packed = a.begin(packed_rows);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t item = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
-    const int64_t tc = item / k;
-    const int32_t j = (int32_t)(item - tc * k);
-    const int64_t t = tc / pg.chunks;
-    if (t >= T)
+    const uint32_t item = blockIdx.x * (blockDim.x / kWave) + wave;
+    const uint32_t tc = ONCE ? item : a.geom.k.div(item), j = ONCE ? 0 : item - tc * a.k;
+    const uint32_t t = a.geom.chunks.div(tc);
+    if (t >= a.T)
         return;
-    const int32_t g0 = (int32_t)(tc - t * pg.chunks) * pg.gpc;
-    const int32_t ng = EXACT ? U : min(pg.gpc, pg.G - g0);  // wave-uniform, >= 1
-    const int64_t p = slot_pos[t * k + j];
-    if (p < 0 || p >= max_rows)
+    const int64_t p = slot_pos[(int64_t)t * a.k + j];
+    if (p < 0 || p >= a.max_rows)
         return;
-    const u32x4 *src = x + t * pg.V;
-    const RowStore<SP> dst(packed + p * pg.V + g0 * kWave, (uint32_t)(pg.V - g0 * kWave) * 16u);
+    u32x4 *const row = packed + p * a.geom.V;
+    const int32_t lead = (int32_t)((uint32_t)(reinterpret_cast<uint64_t>(row) >> 4) & a.geom.lead_mask);
+    const Chunk<U, EDGE> c(a.geom, (int32_t)(tc - t * a.geom.chunks.d), threadIdx.x & (kWave - 1), lead);
+    const u32x4 *src = x + (int64_t)t * c.V;
     u32x4 d[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        d[u] = src[EXACT ? (g0 + u) * kWave + lane : load_index(g0, u, ng, lane, pg.V)];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (EXACT || store_ok(g0, u, ng, lane, pg.V))
-            dst.put(d[u], u * kWave + lane);
-    if (fence_system)
+    for (int u = 0; u < U; ++u) {
+        const u32x4 *v = src + c.load_index(u);
+        d[u] = ONCE ? __builtin_nontemporal_load(v) : *v;
+    }
+    c.template store<RowStore<SP>>(d, row);
+    if (a.fence_system)
         __threadfence_system();
 }
 
-template <int U, bool EXACT, int SP>
-void launch_pack_u(bool per_slot, dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts, const u32x4 *x, int64_t T,
-                   const PackGeom &pg, int32_t k, const int32_t *slot_pos, u32x4 *packed, int64_t max_rows,
-                   uint32_t *epoch_word, uint32_t epoch, RoundSel sel, bool fence_system) {
-    if (per_slot)
-        hipExtLaunchKernelGGL(pack_slot_kernel<U, EXACT, SP>, grid, block, 0, stream, ts.start, ts.stop, 0, x, T, pg,
-                              k, slot_pos, packed, max_rows, epoch_word, epoch, sel, fence_system);
+struct PackPtrs {
+    const u32x4 *x;
+    const int32_t *slot_pos;
+    u32x4 *packed;
+};
+
+template <int U, int EDGE, int SP>
+void launch_pack_u(dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts, const PackPtrs &p,
+                   const PackArgs &a) {
+    if (a.k == 1)
+        hipExtLaunchKernelGGL((pack_kernel<U, EDGE, SP, true>), grid, block, 0, stream, ts.start, ts.stop, 0, p.x,
+                              p.slot_pos, p.packed, a);
     else
-        hipExtLaunchKernelGGL(pack_kernel<U, EXACT, SP>, grid, dim3(256), 0, stream, ts.start, ts.stop, 0, x, T, pg, k,
-                              slot_pos, packed, max_rows, epoch_word, epoch, sel, fence_system);
+        hipExtLaunchKernelGGL((pack_kernel<U, EDGE, SP, false>), grid, block, 0, stream, ts.start, ts.stop, 0, p.x,
+                              p.slot_pos, p.packed, a);
 }
 
-// Chunk lengths with an EXACT instance (groups of 64 vectors), longest first.
-constexpr int kExactU[] = {16, 15, 14, 13, 12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1};
+constexpr int kMaxU = 16;  // longest chunk: 16 KiB
 
-// Launches the instance for chunk length `exact` (0: generic) under store policy SP.
-template <int SP>
-void launch_chunk(int exact, bool per_slot, dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts, const u32x4 *x,
-                  int64_t T, const PackGeom &pg, int32_t k, const int32_t *slot_pos, u32x4 *packed, int64_t max_rows,
-                  uint32_t *epoch_word, uint32_t epoch, RoundSel sel, bool fence_system) {
-#define EP_PACK_ARGS per_slot, grid, block, stream, ts, x, T, pg, k, slot_pos, packed, max_rows, epoch_word, epoch, sel, fence_system
-    switch (exact) {
-    case 16: launch_pack_u<16, true, SP>(EP_PACK_ARGS); break;
-    case 15: launch_pack_u<15, true, SP>(EP_PACK_ARGS); break;
-    case 14: launch_pack_u<14, true, SP>(EP_PACK_ARGS); break;
-    case 13: launch_pack_u<13, true, SP>(EP_PACK_ARGS); break;
-    case 12: launch_pack_u<12, true, SP>(EP_PACK_ARGS); break;
-    case 11: launch_pack_u<11, true, SP>(EP_PACK_ARGS); break;
-    case 10: launch_pack_u<10, true, SP>(EP_PACK_ARGS); break;
-    case 9: launch_pack_u<9, true, SP>(EP_PACK_ARGS); break;
-    case 8: launch_pack_u<8, true, SP>(EP_PACK_ARGS); break;
-    case 7: launch_pack_u<7, true, SP>(EP_PACK_ARGS); break;
-    case 6: launch_pack_u<6, true, SP>(EP_PACK_ARGS); break;
-    case 5: launch_pack_u<5, true, SP>(EP_PACK_ARGS); break;
-    case 4: launch_pack_u<4, true, SP>(EP_PACK_ARGS); break;
-    case 3: launch_pack_u<3, true, SP>(EP_PACK_ARGS); break;
-    case 2: launch_pack_u<2, true, SP>(EP_PACK_ARGS); break;
-    case 1: launch_pack_u<1, true, SP>(EP_PACK_ARGS); break;
-    default:
-        if (pg.gpc > 4)
-            launch_pack_u<16, false, SP>(EP_PACK_ARGS);
-        else
-            launch_pack_u<4, false, SP>(EP_PACK_ARGS);
+// Launches the instance for chunks of `u` whole groups (0: the ragged instance).
+template <int SP, int U = kMaxU>
+void launch_chunk(int u, bool partial, dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts,
+                  const PackPtrs &p, const PackArgs &a) {
+    if (u == 0)
+        return launch_pack_u<kMaxU, kRagged, SP>(grid, block, stream, ts, p, a);
+    if (u != U) {
+        if constexpr (U > 1)
+            launch_chunk<SP, U - 1>(u, partial, grid, block, stream, ts, p, a);
+        return;
     }
-#undef EP_PACK_ARGS
+    if (partial)
+        launch_pack_u<U, kPartial, SP>(grid, block, stream, ts, p, a);
+    else
+        launch_pack_u<U, kWhole, SP>(grid, block, stream, ts, p, a);
+}
+
+// Store policy of a launch that packs `bytes` bytes of rows of row_bytes, by the time of
+// whole passes (layout, pack, combine; buffers rotated past the memory-side cache), since
+// what a policy leaves in the caches is paid for by the next kernel.  Measured on MI355X,
+// non-temporal / kStoreWT / kStoreWTStream:
+//   rows of whole 64-byte pieces: 52 MiB of 2 KiB rows 33.9 / 38.2 / 33.8 us, 268 MiB of 4 KiB
+//     rows 109.2 / 121.4 / 108.2; of 14 KiB rows 437 MiB 190.6 / 199 / 190.3, 875 MiB 398 / 388 /
+//     391, 1312 MiB 564 / 556 / 553, 2187 MiB 970 / 947 / 960, 3584 MiB 1525 / 1489 / 1484;
+//   other rows, whose ends share a cache line with their neighbours': 17 MiB of 5776 B rows
+//     13.7 / 13.1 / 14.9 us, 35 MiB of 2064 B rows 30.4 / 28.5 / 33.8, 93 MiB of 8208 B rows 54 /
+//     71 / 62, 875 MiB of 14352 B rows 435 / 520 / 484, 2189 MiB 1069 / 1330 / 1195.
+// Rows to host memory (graph rounds) go non-temporal.
+int pack_policy(int64_t bytes, int64_t row_bytes, bool to_host) {
+    if (to_host)
+        return kStoreNT;
+    if (row_bytes % 64 != 0)
+        return bytes < (40ll << 20) ? kStoreWT : kStoreNT;
+    return bytes < (128ll << 20) ? kStoreNT : kStoreWTStream;
 }
 
 }  // namespace
@@ -185,53 +189,60 @@ hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int
                        hipStream_t stream, RoundSel sel, bool fence_system) {
     if (T == 0)
         return hipSuccess;
-    PackGeom pg;
-    pg.V = H / 8;
-    pg.G = (pg.V + kWave - 1) / kWave;
-    const bool per_slot = k >= 4;
-    int exact = 0;  // chunk length of the EXACT instance, 0: generic
-    if (pg.V % kWave == 0)
-        for (int u : kExactU)
-            if (pg.G % u == 0) {
-                exact = u >= (pg.G < 4 ? pg.G : 4) ? u : 0;  // no short chunks for long rows
-                break;
-            }
+    const int32_t V = H / 8, lead_mask = V % 8 ? 7 : 0, G = (V + lead_mask + kWave - 1) / kWave;
+    const int64_t rows = T * k;  // waves per chunk of a row
+    // chunk length: the largest divisor of G, no short chunks for long rows (0: ragged)
+    int u = std::min(G, kMaxU);
+    while (G % u != 0)
+        --u;
+    if (u < std::min(G, 4))
+        u = 0;
     // few tokens: shorter chunks, so that the launch keeps about 1024 waves (measured on
     // MI355X, top-2 of 14 KiB rows: 128 tokens 2.8 against 3.8 us, 512 tokens 5.5 against 6.0)
-    if (exact > 1) {
-        const int64_t per_chunk = per_slot ? T * k : T;
-        if (per_chunk * (pg.G / exact) < 1024)
-            for (int u : kExactU)
-                if (u < exact && pg.G % u == 0) {
-                    exact = u;
-                    if (per_chunk * (pg.G / u) >= 1024)
-                        break;
-                }
-    }
-    pg.gpc = exact ? exact : (pg.G < 16 ? pg.G : 16);
-    pg.chunks = (pg.G + pg.gpc - 1) / pg.gpc;
-    const int64_t items = (per_slot ? T * k : T) * pg.chunks;
+    for (int v = u - 1; v >= 1 && rows * (G / u) < 1024; --v)
+        if (G % v == 0)
+            u = v;
+    PackArgs a;
+    a.geom.V = V;
+    a.geom.G = G;
+    a.geom.lead_mask = (uint32_t)lead_mask;
+    a.geom.gpc = u ? u : kMaxU;
+    a.geom.chunks = fast_div((uint32_t)((G + a.geom.gpc - 1) / a.geom.gpc));
+    a.geom.k = fast_div((uint32_t)k);
+    a.k = k;
+    a.max_rows = max_rows;
+    a.epoch_word = epoch_word;
+    a.epoch = epoch;
+    a.sel = sel;
+    a.fence_system = fence_system;
     // per-slot waves of one token chunk share its row through L2 only inside one workgroup
-    // (consecutive workgroups run on different XCDs, each with its own L2): for k = 8 or 16
-    // a workgroup of k waves holds them all, so the row is fetched from HBM once (4-wave
-    // workgroups fetched it twice at k = 8; measured on MI355X)
-    const int waves = per_slot && (k == 8 || k == 16) ? k : 4;
-    const int64_t blocks = (items + waves - 1) / waves;
-    if (blocks > INT32_MAX)
+    // (consecutive workgroups run on different XCDs, each with its own L2): a workgroup of k
+    // waves holds them all, so the row is fetched from HBM once (4-wave workgroups fetched
+    // it twice at k = 8; measured on MI355X)
+    const int waves = k >= 2 && k <= 16 ? k : 4;
+    const int64_t waves_per_token = (int64_t)a.geom.chunks.d * k;
+    // launches of at most 2^31 waves (what FastDiv divides); one for any real layer
+    const int64_t per = std::min<int64_t>(T, (INT32_MAX - waves) / waves_per_token);
+    if (per < 1)
         return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
-    const u32x4 *xv = static_cast<const u32x4 *>(x);
-    u32x4 *pv = static_cast<u32x4 *>(packed);
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
-    TraceSlot ts = trace_acquire();
-    const bool wt = T * k * (int64_t)pg.V * 16 >= kWriteThroughBytes;
-    if (wt)
-        launch_chunk<kStoreWTStream>(exact, per_slot, grid, dim3(per_slot ? waves * kWave : 256), stream, ts, xv, T, pg, k,
-                           slot_pos, pv, max_rows, epoch_word, epoch, sel, fence_system);
-    else
-        launch_chunk<kStoreNT>(exact, per_slot, grid, dim3(per_slot ? waves * kWave : 256), stream, ts, xv, T, pg, k,
-                            slot_pos, pv, max_rows, epoch_word, epoch, sel, fence_system);
-    hipError_t err = hipGetLastError();
+    const TraceSlot ts = trace_acquire();
+    const int policy = pack_policy(T * k * (int64_t)V * 16, V * 16, sel.round != nullptr);
+    for (int64_t t0 = 0; t0 < T; t0 += per) {
+        a.T = (uint32_t)std::min(per, T - t0);
+        const PackPtrs p{static_cast<const u32x4 *>(x) + t0 * V, slot_pos + t0 * k, static_cast<u32x4 *>(packed)};
+        const dim3 grid((unsigned)((a.T * waves_per_token + waves - 1) / waves)), block(waves * kWave);
+        TraceSlot part;
+        part.start = t0 == 0 ? ts.start : nullptr;
+        part.stop = t0 + a.T == T ? ts.stop : nullptr;
+        if (policy == kStoreWT)
+            launch_chunk<kStoreWT>(u, V % kWave != 0, grid, block, stream, part, p, a);
+        else if (policy == kStoreWTStream)
+            launch_chunk<kStoreWTStream>(u, V % kWave != 0, grid, block, stream, part, p, a);
+        else
+            launch_chunk<kStoreNT>(u, V % kWave != 0, grid, block, stream, part, p, a);
+    }
+    const hipError_t err = hipGetLastError();
     if (err == hipSuccess)
         trace_submit("pack", ts);
     return err;
