@@ -201,7 +201,29 @@ constexpr int64_t kCombineWriteThroughBelow = 44ll << 20;
 constexpr int64_t kCombineSplitAbove = 128ll << 20;
 constexpr int64_t kCombineLaunchBytes = 64ll << 20;
 
+// LDS a workgroup reserves (and does not use) to limit the workgroups per compute unit, so
+// that about 96 to 128 KiB of row loads are in flight on each: a wave has loads_512 * 512
+// bytes in flight.  More waves at once spread the reads over more rows and HBM pages.
+// Measured on MI355X over whole passes, non-temporal regime, 4-wave workgroups per compute
+// unit (none: as many as fit):
+//   8 loads of 1 KiB (top-8, 14 KiB rows): 32768 tokens, skewed routing none / 4 / 3 / 2 1487 /
+//     1477 / 1448 / 1466 us (the combine 722 -> 685, 6.2 TB/s), uniform 1554 / 1563 / 1545 / 1565;
+//     4000 tokens, skewed 183.5 / 182.3 / 178.7 / 183.2;
+//   16 (top-8, 8 KiB rows), 16384 tokens: 442.6 / 442.1 / 440.4 / 435.1;
+//   14, 12, 10 (top-7, 6, 5, 14 KiB rows), 8192 tokens, none / 2: 359 / 352, 313.8 / 308.1, 266.8 /
+//     262.5; 6 (top-6, 5776 B rows): none / 4 / 2 261 / 256 / 263.
+// Up to four slots it measured no better (top-4: 491.6 / 490.8 / 491.5 / 494.4).
+uint32_t reserved_lds(int32_t k, int loads_512) {
+    if (k <= 4)
+        return 0;
+    const int groups = std::max(2, (48 + loads_512 / 2) / loads_512);  // 96 KiB over 4 waves, rounded
+    if (groups > 4)
+        return 0;
+    return groups == 4 ? 40u << 10 : (groups == 3 ? 52u << 10 : 64u << 10);  // of 160 KiB
+}
+
 struct CombineCall {
+    bool all_rows;  // every slot is expected to have a row
     const void *recv;
     const int32_t *slot_pos;
     const float *topk_w;
@@ -230,6 +252,7 @@ hipError_t launch_ranges(const CombineCall &c, hipStream_t stream) {
     if (per < 1)
         return hipErrorInvalidValue;
     const bool wt = out_bytes < kCombineWriteThroughBelow;
+    const uint32_t lds = c.all_rows && !wt ? reserved_lds(c.k, (F32_OUT ? 1 : 2) * U * KC) : 0;
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
     const TraceSlot ts = trace_acquire();  // one pair of events around every launch of the call
     for (int64_t t0 = 0; t0 < c.T; t0 += per) {
@@ -237,7 +260,7 @@ hipError_t launch_ranges(const CombineCall &c, hipStream_t stream) {
         const dim3 grid((unsigned)((n * chunks.d + kWaves - 1) / kWaves)), block(kWaves * kWave);
         const hipEvent_t start = t0 == 0 ? ts.start : nullptr, stop = t0 + n == c.T ? ts.stop : nullptr;
         auto go = [&](auto kern) {
-            hipExtLaunchKernelGGL(kern, grid, block, 0, stream, start, stop, 0, c.recv, c.slot_pos + t0 * c.k,
+            hipExtLaunchKernelGGL(kern, grid, block, lds, stream, start, stop, 0, c.recv, c.slot_pos + t0 * c.k,
                                   c.topk_w + t0 * c.k, (uint32_t)n, c.V, chunks, c.k,
                                   static_cast<void *>(static_cast<char *>(c.out) + t0 * row_bytes), c.max_rows, c.sel);
         };
@@ -392,10 +415,10 @@ __global__ __launch_bounds__(256) void accumulate_kernel(const u32x4 *__restrict
 
 hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float *topk_w,
                           int64_t T, int32_t H, int32_t k, void *out, bool out_f32,
-                          int64_t max_rows, hipStream_t stream, RoundSel sel) {
+                          int64_t max_rows, hipStream_t stream, bool all_rows, RoundSel sel) {
     if (T == 0)
         return hipSuccess;
-    const CombineCall c{recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
+    const CombineCall c{all_rows, recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
     if (sel.round)  // graph-replayed rounds: the general instance reading the round
         return out_f32 ? launch_ranges<4, 8, true, false, false, true>(c, stream)
                        : launch_ranges<2, 8, false, false, false, true>(c, stream);
