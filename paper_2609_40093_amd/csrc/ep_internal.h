@@ -58,10 +58,9 @@ struct FastDiv {
     __device__ __forceinline__ uint32_t div(uint32_t n) const { return (__umulhi(n, mul) + n) >> shift; }
 };
 inline FastDiv fast_div(uint32_t d) {  // 1 <= d < 2^31
-    uint32_t shift = 0;
-    while ((1ull << shift) < d)
-        ++shift;
-    return {d, (uint32_t)((((1ull << shift) - d) << 32) / d + 1), shift};
+    const uint32_t shift = d > 1 ? 32 - __builtin_clz(d - 1) : 0;
+    const uint64_t rest = (1ull << shift) - d;  // 0 for a power of two: no host division
+    return {d, rest ? (uint32_t)((rest << 32) / d + 1) : 1u, shift};
 }
 
 // ---- layout geometry -----------------------------------------------------------
@@ -145,7 +144,7 @@ struct LayoutArgs {
     int32_t e_lo = 0, all_E = 0;
     // set by launch_layout: experts per rank, division by k, E and E/4
     int32_t L = 0;
-    FastDiv k_div, e_div, e4_div;
+    FastDiv k_div, e_div, e4_div;  // e_div, e4_div: two-kernel layouts only
     int32_t *expert_counts, *expert_offsets, *rank_counts, *rank_offsets;
     int32_t *slot_pos, *row_src;
     uint32_t *status;        // workspace byte 0

@@ -15,21 +15,25 @@
 //      (they do not depend on the layout; vector loads complete in order, so the ids
 //      come first);
 //   B. the workgroup counts all T*k entries (16-byte loads of 4 ids) with LDS atomic
-//      adds into 16 copies of the per-expert counters, chosen by lane, so that lanes of
-//      one instruction naming the same expert rarely hit the same word (vector and LDS
-//      work only: a ballot per id would queue every wave of the compute unit on its one
-//      scalar unit), both over all entries and over the entries before its own range;
-//      routing errors (an id outside [0,E), an expert twice in one token row) are found
-//      in the same pass (a top-8 row spans the 4-id groups of two neighbouring lanes);
+//      adds into histograms of 16 neighbouring counters per expert, chosen by lane (wave.h),
+//      the entries before its own range apart (vector and LDS work only: a ballot per id
+//      would queue every wave of the compute unit on its one scalar unit);
 //   C. the totals' exclusive scan (DPP; a lane per expert, or four consecutive experts
 //      per lane above 64 experts) gives the expert offsets; workgroup 0 stores the
-//      counts, offsets, rank counts/offsets and the status word;
+//      counts, offsets and rank counts/offsets;
 //   D. wave 0 ranks the workgroup's own entries in flat order (ballot match-any and a
 //      masked popcount, as the layout kernel does: stable), stores slot_pos / row_src and
 //      keeps the rows in LDS;
 //   E. each wave stores its tokens' rows (or its part of one) to their k packed rows
 //      (non-temporal; U groups of 64 16-byte vectors, one per lane, all loads in flight
-//      together).
+//      together; loads cached: rows the caller has just written, or reads again, are found
+//      in the memory-side cache).
+// One more workgroup checks the routing (an id outside [0,E), an expert twice in one token
+// row) and stores the status word: in every workgroup beside the counting, with the 16
+// copies as rows of counters in one LDS bank, the kernel took 9.0 us at 256 tokens, top-8 of
+// 256 experts, 14 KiB rows (now 7.4), 20.4 at 2048 tokens, top-8 of 128, 4 KiB rows (16.7), 12.6
+// at 8192 tokens, top-2 of 256, 1 KiB rows (8.6); cached loads took the 4096-token, top-2
+// layer of 8 KiB rows from 34.5 to 32.5 us.
 // The outputs equal those of the layout kernel followed by the pack kernel, bit for bit.
 // Workgroups never wait on each other, so nothing needs them resident together.
 //
@@ -38,8 +42,8 @@
 // top-8), T*k <= 65536 for E <= 64 and k <= 4, else T*k <= 16384 for rows up to 8 KiB and
 // 8192 for longer ones (every workgroup reads and counts every id before its stores:
 // beyond that the layout kernel's exchange of totals costs less), rows of 1, 2, 4, 8, 14
-// or 16 groups (H = 512 * groups), a 16-byte aligned routing array.  The split runs of
-// fewer than 1024 tokens keep the same limits.
+// or 16 groups (H = 512 * groups), under 120 MiB packed for k >= 2, a 16-byte aligned routing
+// array.  The split runs of fewer than 1024 tokens keep the same limits.
 #include "ep_internal.h"
 #include "wave.h"
 
@@ -54,6 +58,11 @@ constexpr int64_t kFMaxSlots = 65536;        // T*k: every workgroup reads every
 // with 4 KiB rows, 20-24 against 23-29 us, and loses with 14 KiB rows, 56 against 55 us)
 constexpr int64_t kFMaxSlotsWide = 16384;    // rows of at most 8 KiB
 constexpr int64_t kFMaxSlotsWideLong = 8192; // longer rows
+// Bytes packed from which the two steps as their own kernels win for k >= 2 (their pack gives
+// every slot its own wave; measured on MI355X, whole passes, one kernel / two: 64 MiB, top-8
+// of 4 KiB rows 29.9 / 34.9 us; 112 MiB, top-8 of 14 KiB 50.6 / 52.6; 128 MiB, top-2 of 8 KiB
+// 73.7 / 70.0, top-4 of 4 KiB 64.1 / 61.2)
+constexpr int64_t kFMaxBytes = 120ll << 20;
 constexpr int kFMaxOwn = 256;                // entries one workgroup owns (LDS rows)
 constexpr int kFOwnRounds = kFMaxOwn / kWave;
 constexpr int kFBatch = 4;                   // 16-byte id loads in flight per lane
@@ -86,20 +95,13 @@ __device__ __forceinline__ void load_ids(const i32x4 *q, int64_t full, int64_t q
         v[b] = q[min(qw + (int64_t)b * threads + lane, full - 1)];
 }
 
-constexpr int kFCopies = 16;  // copies of the LDS counters (lane % 16 picks one)
+constexpr int kFCopies = 16;  // counters per bin of the LDS histograms (hist_index)
 
-// Counts one id into the LDS counters (all entries, and those before this workgroup's);
-// ME counters per copy.
+// Counts one id into an LDS histogram of ME + 1 bins; bin ME takes ids that name no expert.
 template <int ME>
-__device__ __forceinline__ void count_id(int id, bool in, bool before, int E, int *s_all, int *s_pre, int copy,
-                                         bool &bad_id) {
-    const bool valid = in && (unsigned)id < (unsigned)E;
-    bad_id |= in && !valid;
-    if (valid) {
-        atomicAdd(&s_all[copy * ME + id], 1);
-        if (before)
-            atomicAdd(&s_pre[copy * ME + id], 1);
-    }
+__device__ __forceinline__ void count_id(int id, bool in, int E, int *hist, int lane) {
+    const int bin = in && (unsigned)id < (unsigned)E ? id : ME;
+    atomicAdd(&hist[hist_index(bin, kFCopies, lane)], 1);
 }
 
 // Does any id of `a` (in [0,E)) equal one of `b`?  (The two halves of a top-8 row.)
@@ -111,6 +113,53 @@ __device__ __forceinline__ bool halves_repeat(i32x4 a, i32x4 b, int E) {
     return r;
 }
 
+// The routing errors of all entries (an id outside [0,E), an expert twice in one token row),
+// stored to the status word by one workgroup.  A thread holds whole rows: one 4-id group,
+// or two neighbouring ones for top-8.
+template <int K>
+__device__ __forceinline__ void check_routing(const FusedArgs &a, int *s_err, int tid, int threads) {
+    constexpr int kPer = K == 8 ? 2 : 1, kBatch = 4;  // groups per unit, units in flight
+    if (tid == 0)
+        *s_err = 0;
+    __syncthreads();
+    const i32x4 *q = reinterpret_cast<const i32x4 *>(a.topk_idx);
+    const int64_t slots = a.T * K;
+    const int32_t units = (int32_t)(slots / (4 * kPer));
+    bool bad = false, dup = false;
+    auto bad_id = [&](int id) { return (unsigned)id >= (unsigned)a.E; };
+    for (int32_t u0 = tid; u0 < units; u0 += kBatch * threads) {
+        i32x4 v[kBatch][kPer];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)  // a unit past the last reads it again
+#pragma unroll
+            for (int h = 0; h < kPer; ++h)
+                v[b][h] = q[(int64_t)min(u0 + b * threads, units - 1) * kPer + h];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+#pragma unroll
+            for (int h = 0; h < kPer; ++h) {
+                dup |= row_repeats<K == 8 ? 4 : K>(v[b][h], a.E);
+                bad |= bad_id(v[b][h][0]) || bad_id(v[b][h][1]) || bad_id(v[b][h][2]) || bad_id(v[b][h][3]);
+            }
+            if constexpr (K == 8)
+                dup |= halves_repeat(v[b][0], v[b][1], a.E);
+        }
+    }
+    const int64_t i = (int64_t)units * 4 * kPer + tid;  // the last 1..3 ids (whole rows: k <= 2)
+    if (i < slots) {
+        const int id = a.topk_idx[i];
+        bad |= bad_id(id);
+        if (K == 2 && tid == 0)
+            dup |= !bad_id(id) && id == a.topk_idx[i + 1];  // the tail is one row
+    }
+    const uint32_t err = (__ballot(bad) ? kRoutingIdOutOfRange : 0u) | (__ballot(dup) ? kRoutingDuplicate : 0u);
+    if ((tid & (kWave - 1)) == 0 && err)
+        atomicOr(s_err, (int)err);
+    __syncthreads();
+    if (tid == 0)
+        *a.status = (uint32_t)*s_err;
+}
+
 // MULTI: more ids than one batch of the workgroup's loads (the count loops).  Instances
 // without the loop have only straight-line loads, so the compiler's waits stay exact and
 // no wave waits for its token row before the count's barrier.  WIDE: more than 64
@@ -118,14 +167,17 @@ __device__ __forceinline__ bool halves_repeat(i32x4 a, i32x4 b, int E) {
 template <int U, int K, bool MULTI, bool WIDE>
 __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, int32_t tpw, int32_t split) {
     constexpr int ME = WIDE ? kFMaxE : kFNarrowE;  // counters per copy
-    __shared__ int s_all[kFCopies * ME];
-    __shared__ int s_pre[kFCopies * ME];
+    constexpr int kHist = kFCopies * (ME + 1);
+    __shared__ __align__(16) int s_rest[kHist];  // entries from this workgroup's on
+    __shared__ __align__(16) int s_pre[kHist];   // entries before this workgroup's
     __shared__ int s_base[ME];
     __shared__ int s_off[WIDE ? ME + 1 : 1];
     __shared__ int s_pos[kFMaxOwn];
     __shared__ int s_err;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const int threads = blockDim.x, waves = threads / kWave;
+    if (blockIdx.x == gridDim.x - 1)
+        return check_routing<K>(a, &s_err, tid, threads);
     const int64_t slots = a.T * K;
     const int runs = waves / split;  // token runs of tpw tokens (split == 1: one per wave)
     const int64_t tok0 = (int64_t)blockIdx.x * runs * tpw;  // runs*tpw*K: a multiple of 4
@@ -153,25 +205,21 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
     // wait for its token row before the count's barrier)
     const int64_t ti = full * 4 + lane;
     const int tail_id = a.topk_idx[min(ti, slots - 1)];
-    const int tail_next = a.topk_idx[min(ti + 1, slots - 1)];
     const int64_t wtok = tok0 + (int64_t)(w / split) * tpw;
     u32x4 d[U];
     {
         const u32x4 *src = x + min(wtok, tok1 - 1) * V + col + lane;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            d[u] = __builtin_nontemporal_load(src + u * kWave);
+            d[u] = src[u * kWave];
     }
-    for (int i = tid; i < kFCopies * ME; i += threads) {
-        s_all[i] = 0;
-        s_pre[i] = 0;
+    for (int i = tid; i < kHist / 4; i += threads) {
+        reinterpret_cast<i32x4 *>(s_rest)[i] = i32x4{0, 0, 0, 0};
+        reinterpret_cast<i32x4 *>(s_pre)[i] = i32x4{0, 0, 0, 0};
     }
-    if (tid == 0)
-        s_err = 0;
     __syncthreads();
 
     // B. count all entries into the LDS counters
-    bool bad_id = false, dup = false;
     auto count_batch = [&](int64_t qb) {
 #pragma unroll
         for (int b = 0; b < kFBatch; ++b) {
@@ -179,23 +227,11 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
             if (g >= full)
                 break;
             const int64_t qi = g + lane;
-            const bool in = qi < full;
             // entries before this workgroup's: whole 4-id groups (ent0 is a multiple of 4)
-            const bool before = qi * 4 < ent0;
-            if constexpr (K == 8) {
-                // a row is the groups of lanes 2m and 2m+1 (qi and lane have the same
-                // parity; full = 2T is even, so both halves are in or out together)
-                i32x4 o;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    o[c] = __shfl_xor(v[b][c], 1);
-                dup |= in && (row_repeats<4>(v[b], a.E) || ((lane & 1) == 0 && halves_repeat(v[b], o, a.E)));
-            } else {
-                dup |= in && row_repeats<K>(v[b], a.E);
-            }
+            int *hist = qi * 4 < ent0 ? s_pre : s_rest;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                count_id<ME>(v[b][c], in, before, a.E, s_all, s_pre, lane % kFCopies, bad_id);
+                count_id<ME>(v[b][c], qi < full, a.E, hist, lane);
         }
     };
     // the first batch outside the loop: its wait leaves the token row's loads in flight
@@ -207,17 +243,17 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
             count_batch(qw);
         }
     }
-    if (w == 0 && full * 4 < slots) {  // the tail: 1..3 ids (a whole token row for k <= 2)
-        const bool in = ti < slots;
-        const int id = in ? tail_id : -1;
-        if (K == 2 && lane == 0)
-            dup |= (unsigned)id < (unsigned)a.E && id == tail_next;  // the tail is one row
-        count_id<ME>(id, in, ti < ent0, a.E, s_all, s_pre, lane % kFCopies, bad_id);
-    }
-    const uint32_t wave_err = (__ballot(bad_id) ? kRoutingIdOutOfRange : 0u) | (__ballot(dup) ? kRoutingDuplicate : 0u);
-    if (lane == 0 && wave_err)
-        atomicOr(&s_err, (int)wave_err);
+    if (w == 0 && ti < slots)  // the tail: 1..3 ids
+        count_id<ME>(tail_id, true, a.E, ti < ent0 ? s_pre : s_rest, lane);
     __syncthreads();
+    if (WIDE) {  // fold the counters on every wave: totals to s_off, entries before to s_base
+        for (int e = tid; e < a.E; e += threads) {
+            const int p = hist_sum(s_pre, e, kFCopies, lane);
+            s_base[e] = p;
+            s_off[e] = p + hist_sum(s_rest, e, kFCopies, lane);
+        }
+        __syncthreads();
+    }
 
     if (w == 0 && WIDE) {
         // C (wide). Lane l holds experts 4l..4l+3: their totals, one scan of the lanes'
@@ -227,14 +263,8 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int e = 4 * lane + q;
-            tot[q] = pre[q] = 0;
-            if (e < a.E) {
-#pragma unroll
-                for (int c = 0; c < kFCopies; ++c) {
-                    tot[q] += s_all[c * ME + e];
-                    pre[q] += s_pre[c * ME + e];
-                }
-            }
+            pre[q] = e < a.E ? s_base[e] : 0;
+            tot[q] = e < a.E ? s_off[e] : 0;
             sum += tot[q];
         }
         const int incl = wave_inclusive_scan(sum);
@@ -265,22 +295,13 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
                 if (r < a.R)
                     a.rank_counts[r] = s_off[(r + 1) * L] - s_off[r * L];
             }
-            if (lane == 0) {
-                *a.status = (uint32_t)s_err;
-                if (a.epoch_word)
-                    *a.epoch_word = a.epoch;
-            }
+            if (lane == 0 && a.epoch_word)
+                *a.epoch_word = a.epoch;
         }
     } else if (w == 0) {
         // C. totals, offsets; workgroup 0 stores the layout's counts and the status
-        int tot = 0, pre = 0;
-        if (lane < a.E) {
-#pragma unroll
-            for (int c = 0; c < kFCopies; ++c) {
-                tot += s_all[c * ME + lane];
-                pre += s_pre[c * ME + lane];
-            }
-        }
+        const int pre = lane < a.E ? hist_sum(s_pre, lane, kFCopies, lane) : 0;
+        const int tot = lane < a.E ? pre + hist_sum(s_rest, lane, kFCopies, lane) : 0;
         const int incl = wave_inclusive_scan(tot);
         const int excl = incl - tot;
         const int total = __shfl(incl, kWave - 1);
@@ -308,7 +329,6 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
                     a.expert_offsets[kWave] = total;
                 if (a.R == kWave)
                     a.rank_offsets[kWave] = total;
-                *a.status = (uint32_t)s_err;
                 if (a.epoch_word)
                     *a.epoch_word = a.epoch;
             }
@@ -355,7 +375,7 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
             const u32x4 *src = x + t * V + col + lane;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                d[u] = __builtin_nontemporal_load(src + u * kWave);
+                d[u] = src[u * kWave];
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -373,8 +393,8 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
 template <int U, int K, bool MULTI, bool WIDE>
 void launch_one(const FusedArgs &a, int32_t tpw, int32_t split, unsigned blocks, int threads, hipStream_t stream,
                 TraceSlot ts) {
-    hipExtLaunchKernelGGL((layout_pack_kernel<U, K, MULTI, WIDE>), dim3(blocks), dim3(threads), 0, stream, ts.start,
-                          ts.stop, 0, a, tpw, split);
+    hipExtLaunchKernelGGL((layout_pack_kernel<U, K, MULTI, WIDE>), dim3(blocks + 1), dim3(threads), 0, stream,
+                          ts.start, ts.stop, 0, a, tpw, split);  // the last workgroup checks the routing
 }
 
 // Picks the instance: the count loop only where one batch of loads does not cover every
@@ -471,6 +491,8 @@ bool fused_layout_pack_fits(int64_t T, int32_t k, int32_t E, int32_t H, const vo
     if (T * k > (E > kFNarrowE || k == 8 ? wide_limit : kFMaxSlots))
         return false;
     if (H % 512 != 0)
+        return false;
+    if (k > 1 && T * k * (int64_t)H * 2 >= kFMaxBytes)
         return false;
     const int G = H / 512;
     return (G == 1 || G == 2 || G == 4 || G == 8 || G == 14 || G == 16) &&

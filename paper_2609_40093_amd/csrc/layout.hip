@@ -569,13 +569,15 @@ void launch_one(const LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
 }
 
 template <int K>
-void launch_layout_k(const LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
+void launch_layout_k(LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
     if (K != 0 && a.slots <= kLayoutOneKernelIds)
         return launch_one<4, K>(a, stream, ts);
     const LayoutGeom g = layout_geometry(a.slots, a.E);
     if constexpr (K == 0)  // as many threads as fit, for the checks of general rows
         if (g.tiles == 1)
             return g.waves == 16 ? launch_one<16, K>(a, stream, ts) : launch_one<4, K>(a, stream, ts);
+    a.e_div = fast_div((uint32_t)a.E);
+    a.e4_div = fast_div((uint32_t)std::max(1, a.E / 4));
     const int64_t tile_entries = (int64_t)g.waves * kWave * g.rounds;
     const unsigned count_threads = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(256, tile_entries / 8 / kWave * kWave));
     const size_t count_lds = sizeof(int) * ((size_t)hist_copies(a.E) * (a.E + 1) + 1);
@@ -593,8 +595,6 @@ void launch_layout_k(const LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
 hipError_t launch_layout(LayoutArgs a, hipStream_t stream) {
     a.L = a.E / a.R;
     a.k_div = fast_div((uint32_t)a.k);
-    a.e_div = fast_div((uint32_t)a.E);
-    a.e4_div = fast_div((uint32_t)std::max(1, a.E / 4));
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
     const TraceSlot ts = trace_acquire();
     switch (a.k) {
