@@ -66,11 +66,21 @@ def _stream_ptr(stream=None) -> int:
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
+def _current_stream(stream) -> int:
+    """_stream_ptr for calls that hold a device tensor (the device is initialised)."""
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(_get_device())
+    return _stream_ptr(stream)
+
+
 def _ptr(t: Optional[torch.Tensor]):
-    return t.data_ptr() if t is not None and t.numel() else None
+    return t.data_ptr() if t is not None else None  # 0 for a tensor without elements
 
 
 def _need(t: torch.Tensor, name: str, dtypes, ndim=None):
+    if (t.is_cuda and t.dtype in dtypes and t.is_contiguous() and (ndim is None or t.dim() == ndim)
+            and t.get_device() == _get_device()):
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.device.index != _get_device():
@@ -108,8 +118,8 @@ class Layout:
 def _layout_buffers(T: int, k: int, num_experts: int, num_ranks: int, dev, with_row_src: bool,
                     out: Optional[Layout]) -> Layout:
     """The layout's output tensors and zero-filled workspace (reused when `out` fits)."""
-    if out is not None and (out.num_tokens, out.topk, out.num_experts, out.num_ranks) == (T, k, num_experts,
-                                                                                          num_ranks):
+    if (out is not None and out.num_tokens == T and out.topk == k and out.num_experts == num_experts
+            and out.num_ranks == num_ranks):
         return out
     i32 = dict(dtype=torch.int32, device=dev)
     return Layout(T, k, num_experts, num_ranks,
@@ -130,7 +140,7 @@ def dispatch_layout(topk_idx: torch.Tensor, num_experts: int, num_ranks: int, *,
     st = _lib_handle().ep_dispatch_layout(
         _ptr(topk_idx), T, k, num_experts, num_ranks, _ptr(out.expert_counts), _ptr(out.expert_offsets),
         _ptr(out.rank_counts), _ptr(out.rank_offsets), _ptr(out.slot_pos), _ptr(out.row_src),
-        _ptr(out.workspace), out.workspace.numel(), _stream_ptr(stream))
+        _ptr(out.workspace), out.workspace.numel(), _current_stream(stream))
     _check(st, "ep_dispatch_layout")
     return out
 
@@ -169,7 +179,7 @@ def dispatch_layout_local(topk_idx: torch.Tensor, num_experts: int, e_lo: int, e
                           torch.zeros(max(ws, 256), dtype=torch.uint8, device=dev))
     _check(_lib_handle().ep_dispatch_layout_local(
         _ptr(topk_idx), N, k, num_experts, e_lo, e_hi, _ptr(out.local_counts), _ptr(out.local_offsets),
-        _ptr(out.slot_pos), _ptr(out.row_src), _ptr(out.workspace), out.workspace.numel(), _stream_ptr(stream)),
+        _ptr(out.slot_pos), _ptr(out.row_src), _ptr(out.workspace), out.workspace.numel(), _current_stream(stream)),
         "ep_dispatch_layout_local")
     return out
 
@@ -182,7 +192,7 @@ def pack(x: torch.Tensor, slot_pos: torch.Tensor, out: torch.Tensor, *, topk: in
     N, H = x.shape
     if out.shape[1] != H or slot_pos.numel() != N * topk:
         raise ValueError("shape mismatch between x, out and slot_pos")
-    _check(_lib_handle().ep_pack(_ptr(x), N, H, topk, _ptr(slot_pos), _ptr(out), out.shape[0], _stream_ptr(stream)),
+    _check(_lib_handle().ep_pack(_ptr(x), N, H, topk, _ptr(slot_pos), _ptr(out), out.shape[0], _current_stream(stream)),
            "ep_pack")
     return out
 
@@ -201,7 +211,7 @@ def combine_rows(y: torch.Tensor, slot_pos: torch.Tensor, topk_w: torch.Tensor, 
     if y.numel() and y.shape[1] != H or slot_pos.numel() != N * k or out.shape[0] != N:
         raise ValueError("shape mismatch between y, out, topk_w and slot_pos")
     _check(_lib_handle().ep_combine_rows(_ptr(y), y.shape[0] if y.numel() else 0, _ptr(slot_pos), _ptr(topk_w), N, H,
-                                         k, _ptr(out), code, _stream_ptr(stream)), "ep_combine_rows")
+                                         k, _ptr(out), code, _current_stream(stream)), "ep_combine_rows")
     return out
 
 
@@ -333,7 +343,7 @@ def dispatch(x: torch.Tensor, slot_pos: torch.Tensor, staging: Staging, *, topk:
     if slot_pos.numel() != T * topk:
         raise ValueError("slot_pos must hold T*topk entries")
     _check(_lib_handle().ep_dispatch(_ptr(x), T, H, topk, _ptr(slot_pos), _offsets_ptr(rank_offsets, staging),
-                                     staging.handle, buf, epoch & 0xFFFFFFFF, _stream_ptr(stream)), "ep_dispatch")
+                                     staging.handle, buf, epoch & 0xFFFFFFFF, _current_stream(stream)), "ep_dispatch")
 
 
 def dispatch_fused(x: torch.Tensor, topk_idx: torch.Tensor, num_experts: int, num_ranks: int, staging: Staging, *,
@@ -344,14 +354,15 @@ def dispatch_fused(x: torch.Tensor, topk_idx: torch.Tensor, num_experts: int, nu
     _need(topk_idx, "topk_idx", (torch.int32,), 2)
     _need(x, "x", _PAYLOAD_DTYPES, 2)
     T, k = topk_idx.shape
-    if x.shape[0] != T:
+    tokens, H = x.shape
+    if tokens != T:
         raise ValueError("x and topk_idx must have the same number of tokens")
     out = _layout_buffers(T, k, num_experts, num_ranks, topk_idx.device, with_row_src, out)
     _check(_lib_handle().ep_dispatch_fused(
         _ptr(topk_idx), T, k, num_experts, num_ranks, _ptr(out.expert_counts), _ptr(out.expert_offsets),
         _ptr(out.rank_counts), _ptr(out.rank_offsets), _ptr(out.slot_pos), _ptr(out.row_src),
-        _ptr(out.workspace), out.workspace.numel(), _ptr(x), x.shape[1], staging.handle, buf, epoch & 0xFFFFFFFF,
-        _stream_ptr(stream)), "ep_dispatch_fused")
+        _ptr(out.workspace), out.workspace.numel(), _ptr(x), H, staging.handle, buf, epoch & 0xFFFFFFFF,
+        _current_stream(stream)), "ep_dispatch_fused")
     return out
 
 
@@ -372,11 +383,11 @@ def combine(staging: Staging, slot_pos: torch.Tensor, topk_w: torch.Tensor, *, o
     else:
         raise ValueError("out must be bf16 (or 16-bit bits) or float32")
     _need(out, "out", (out.dtype,), 2)
-    if tuple(out.shape) != (T, H) or slot_pos.numel() != T * k:
+    if out.shape != (T, H) or slot_pos.numel() != T * k:
         raise ValueError("shape mismatch between out, topk_w and slot_pos")
     _check(_lib_handle().ep_combine(staging.handle, buf, epoch & 0xFFFFFFFF, _ptr(slot_pos),
                                     _offsets_ptr(rank_offsets, staging), _ptr(topk_w), T, H, k,
-                                    _ptr(out), code, _stream_ptr(stream)), "ep_combine")
+                                    _ptr(out), code, _current_stream(stream)), "ep_combine")
     return out
 
 
