@@ -90,7 +90,7 @@ struct Chunk {
 };
 
 // The arrays are arguments of their own (restrict-qualified: the positions are then scalar
-// loads; as vector loads they cost the 32768-token, top-8 pack of 14 KiB rows 5%).
+// loads; with vector loads the 32768-token, top-8 pack of 14 KiB rows took 804 us, so 752).
 struct PackArgs {
     uint32_t T;  // tokens of this launch
     int32_t k;
