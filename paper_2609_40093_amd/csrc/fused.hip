@@ -32,8 +32,10 @@
 // row) and stores the status word: in every workgroup beside the counting, with the 16
 // copies as rows of counters in one LDS bank, the kernel took 9.0 us at 256 tokens, top-8 of
 // 256 experts, 14 KiB rows (now 7.4), 20.4 at 2048 tokens, top-8 of 128, 4 KiB rows (16.7), 12.6
-// at 8192 tokens, top-2 of 256, 1 KiB rows (8.6); cached loads took the 4096-token, top-2
-// layer of 8 KiB rows from 34.5 to 32.5 us.
+// at 8192 tokens, top-2 of 256, 1 KiB rows (8.6).  Cached against non-temporal row loads, the
+// 4096-token, top-2 layer of 8 KiB rows: 32.6 against 35.6 us where part of the rows is still
+// in the memory-side cache, 36.6 against 35.5 where none is (the combine after it 17.2 against
+// 16.0); cached, since a program packs rows that it has just written.
 // The outputs equal those of the layout kernel followed by the pack kernel, bit for bit.
 // Workgroups never wait on each other, so nothing needs them resident together.
 //
