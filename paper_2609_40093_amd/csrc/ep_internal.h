@@ -106,6 +106,32 @@ inline LayoutGeom layout_geometry(int64_t slots, int32_t experts) {
     return {waves, (int)rounds, tiles};
 }
 
+// The rank kernel's workgroups, `threads` threads each: a tile is cut into `runs` runs, one
+// per workgroup, of `rounds` rounds of 64 entries per wave.
+struct LayoutRuns {
+    unsigned runs;
+    int32_t rounds;
+};
+inline LayoutRuns layout_runs(uint32_t tile_entries, int64_t tiles, int threads) {
+    const int64_t tile_rounds = ((int64_t)tile_entries + threads - 1) / threads;
+    const int64_t splits = std::min<int64_t>(tile_rounds, std::max<int64_t>(1, kLayoutRankGroups / tiles));
+    const int64_t rounds = (tile_rounds + splits - 1) / splits;
+    return {(unsigned)((tile_rounds + rounds - 1) / rounds), (int32_t)rounds};
+}
+// The entries [begin, end) that wave w of a tile's run number `run` ranks, out of n.  Rounds
+// need not divide a tile: its last run ends with the tile, so that every entry has one wave.
+struct EntryRange {
+    uint32_t begin, end;
+};
+__host__ __device__ inline EntryRange layout_wave_run(uint32_t tile, uint32_t tile_entries, uint32_t run,
+                                                      int32_t rounds, int threads, int w, uint32_t n) {
+    const uint32_t tile_begin = tile * tile_entries, per_wave = (uint32_t)rounds * kWave;
+    const uint32_t tile_end = n - tile_begin < tile_entries ? n : tile_begin + tile_entries;
+    const uint32_t begin = tile_begin + run * ((uint32_t)rounds * threads) + w * per_wave;
+    const uint32_t end = begin + per_wave;
+    return {begin < tile_end ? begin : tile_end, end < tile_end ? end : tile_end};
+}
+
 // Routing status bits left in the layout workspace's status word.
 constexpr uint32_t kRoutingIdOutOfRange = 1u;
 constexpr uint32_t kRoutingDuplicate = 2u;

@@ -239,56 +239,54 @@ __device__ __forceinline__ void write_position(const LayoutArgs &a, uint32_t i, 
         a.row_src[pos] = (int32_t)i;
 }
 
-// Counts a wave's run of `rounds` rounds of 64 entries into its counter row cnt [E] (zeroed
-// by the caller).  Cached runs (ids in registers) keep each entry's in-wave rank in rank[]
-// for the positions.
-__device__ __forceinline__ void count_run(const LayoutArgs &a, uint32_t run_begin, int rounds, int lane, int *cnt,
+// Counts a wave's run, the entries [run.begin, run.end) in up to `rounds` rounds of 64, into
+// its counter row cnt [E] (zeroed by the caller).  Cached runs (ids in registers) keep each
+// entry's in-wave rank in rank[] for the positions.
+__device__ __forceinline__ void count_run(const LayoutArgs &a, EntryRange run, int rounds, int lane, int *cnt,
                                           const int (&ids)[kLayoutRankCache], int (&rank)[kLayoutRankCache]) {
-    const uint32_t n = (uint32_t)a.slots;
     if (rounds <= kLayoutRankCache) {
 #pragma unroll
         for (int r = 0; r < kLayoutRankCache; ++r) {
-            if (r >= rounds || run_begin + r * kWave >= n)
+            if (r >= rounds || run.begin + r * kWave >= run.end)
                 break;
-            rank[r] = rank_entry(a, ids[r], run_begin + r * kWave + lane < n, cnt);
+            rank[r] = rank_entry(a, ids[r], run.begin + r * kWave + lane < run.end, cnt);
         }
     } else {
-        int next = run_begin + lane < n ? a.topk_idx[run_begin + lane] : -1;
+        int next = run.begin + lane < run.end ? a.topk_idx[run.begin + lane] : -1;
         for (int r = 0; r < rounds; ++r) {
-            const uint32_t i = run_begin + r * kWave + lane;
-            if (i - lane >= n)
+            const uint32_t i = run.begin + r * kWave + lane;
+            if (i - lane >= run.end)
                 break;
             const int id = next;
-            next = r + 1 < rounds && i + kWave < n ? a.topk_idx[i + kWave] : -1;
-            (void)rank_entry(a, id, i < n, cnt);
+            next = r + 1 < rounds && i + kWave < run.end ? a.topk_idx[i + kWave] : -1;
+            (void)rank_entry(a, id, i < run.end, cnt);
         }
     }
 }
 
 // Writes the run's positions from base[E] (the wave's first row per expert) and the ranks
 // kept by count_run (cached runs) or found again (longer runs).
-__device__ __forceinline__ void write_run(const LayoutArgs &a, uint32_t run_begin, int rounds, int lane, int *base,
+__device__ __forceinline__ void write_run(const LayoutArgs &a, EntryRange run, int rounds, int lane, int *base,
                                           const int (&ids)[kLayoutRankCache], const int (&rank)[kLayoutRankCache]) {
-    const uint32_t n = (uint32_t)a.slots;
     if (rounds <= kLayoutRankCache) {
 #pragma unroll
         for (int r = 0; r < kLayoutRankCache; ++r) {
-            const uint32_t i = run_begin + r * kWave + lane;
-            if (r >= rounds || i - lane >= n)
+            const uint32_t i = run.begin + r * kWave + lane;
+            if (r >= rounds || i - lane >= run.end)
                 break;
-            if (i < n)
+            if (i < run.end)
                 write_position(a, i, rank[r] >= 0 ? base[ids[r] - a.e_lo] + rank[r] : -1);
         }
     } else {
-        int next = run_begin + lane < n ? a.topk_idx[run_begin + lane] : -1;
+        int next = run.begin + lane < run.end ? a.topk_idx[run.begin + lane] : -1;
         for (int r = 0; r < rounds; ++r) {
-            const uint32_t i = run_begin + r * kWave + lane;
-            if (i - lane >= n)
+            const uint32_t i = run.begin + r * kWave + lane;
+            if (i - lane >= run.end)
                 break;
             const int id = next;
-            next = r + 1 < rounds && i + kWave < n ? a.topk_idx[i + kWave] : -1;
-            const int pos = rank_entry(a, id, i < n, base);  // base row + rank so far
-            if (i < n)
+            next = r + 1 < rounds && i + kWave < run.end ? a.topk_idx[i + kWave] : -1;
+            const int pos = rank_entry(a, id, i < run.end, base);  // base row + rank so far
+            if (i < run.end)
                 write_position(a, i, pos);
         }
     }
@@ -474,7 +472,7 @@ __global__ __launch_bounds__(W * 64) void layout_rank_kernel(LayoutArgs a, uint3
     const uint32_t own_begin = tile_begin + blockIdx.x * (kThreads * rounds);
     if (own_begin >= min(tile_begin + tile_entries, n) && !first)
         return;  // the last tile may hold fewer runs
-    const uint32_t run_begin = own_begin + w * rounds * kWave;
+    const EntryRange run = layout_wave_run(tile, tile_entries, blockIdx.x, rounds, kThreads, w, n);
 
     // the ids are loaded up front: the first of those to histogram, and this wave's own
     // (cached runs)
@@ -486,8 +484,8 @@ __global__ __launch_bounds__(W * 64) void layout_rank_kernel(LayoutArgs a, uint3
         for (int r = 0; r < kLayoutRankCache; ++r) {
             if (r >= rounds)
                 break;
-            const uint32_t i = run_begin + r * kWave + lane;
-            ids[r] = i < n ? a.topk_idx[i] : -1;
+            const uint32_t i = run.begin + r * kWave + lane;
+            ids[r] = i < run.end ? a.topk_idx[i] : -1;
         }
     }
     for (int i = tid; i < zeroed / 4; i += kThreads)
@@ -508,7 +506,7 @@ __global__ __launch_bounds__(W * 64) void layout_rank_kernel(LayoutArgs a, uint3
         }
     }
     visit_ids<0, false, true, false>(a, tile_begin, hist_end, own_begin, tid, kThreads, hist_pre, hist_all, err, batch);
-    count_run(a, run_begin, rounds, lane, wave_cnt + w * E, ids, rank);
+    count_run(a, run, rounds, lane, wave_cnt + w * E, ids, rank);
     __syncthreads();
 
     if (ONE || (copies > 1 && own_begin > tile_begin))
@@ -541,21 +539,17 @@ __global__ __launch_bounds__(W * 64) void layout_rank_kernel(LayoutArgs a, uint3
         }
     }
     __syncthreads();
-    write_run(a, run_begin, rounds, lane, wave_cnt + w * E, ids, rank);
+    write_run(a, run, rounds, lane, wave_cnt + w * E, ids, rank);
 }
 
 template <int W>
 void launch_rank(const LayoutArgs &a, const LayoutGeom &g, hipStream_t stream, TraceSlot ts) {
     constexpr int kThreads = W * kWave;
     const uint32_t tile_entries = (uint32_t)(g.waves * kWave * g.rounds);
-    // runs of a tile, in rounds of the whole workgroup
-    const int64_t tile_rounds = (tile_entries + kThreads - 1) / kThreads;
-    const int64_t splits = std::min<int64_t>(tile_rounds, std::max<int64_t>(1, kLayoutRankGroups / g.tiles));
-    const int64_t rounds = (tile_rounds + splits - 1) / splits;
-    const unsigned runs = (unsigned)((tile_rounds + rounds - 1) / rounds);
-    hipExtLaunchKernelGGL((layout_rank_kernel<W, false, 0>), dim3(runs, (unsigned)g.tiles), dim3(kThreads),
+    const LayoutRuns r = layout_runs(tile_entries, g.tiles, kThreads);
+    hipExtLaunchKernelGGL((layout_rank_kernel<W, false, 0>), dim3(r.runs, (unsigned)g.tiles), dim3(kThreads),
                           (uint32_t)rank_lds_bytes<W, false>(a.E), stream, nullptr, ts.stop, 0, a, tile_entries,
-                          (int32_t)rounds);
+                          r.rounds);
 }
 
 // The whole layout in one kernel: the runs, and the workgroup that checks the routing.

@@ -19,6 +19,7 @@ ONE = 20480  # entries up to which one kernel does the layout (k of 1, 2, 4, 8)
 CASES = [(T, E, k) for k in (1, 2, 4, 8) for T, E in ((ONE // k - 1, 96), (ONE // k, 257), (ONE // k + 1, 130))]
 CASES += [(1365, 60, 3), (1366, 60, 3), (683, 513, 6), (7, 600, 5),            # general rows, at one tile's end
           (131072 // 8 + 3, 256, 8), (131072 // 4, 64, 4), (40001, 33, 3),     # 4- and 16-wave runs
+          (100000, 160, 3), (36864, 512, 8),                                   # a tile's last run ends with the tile
           (60000, 300, 8), (9000, 2047, 8), (33001, 2048, 2), (300, 2048, 64), (70, 100, 96)]
 
 
