@@ -72,9 +72,14 @@ inline FastDiv fast_div(uint32_t d) {  // 1 <= d < 2^31
 // waits for another, so the tile count is not tied to the device.
 constexpr int kMaxExperts = 2048;
 // Entries up to which one kernel does the whole layout, each workgroup histogramming every
-// entry (top-k of 1, 2, 4 or 8; one tile for other k, whose routing checks take longer).
-// Measured on MI355X, layouts back to back, one kernel against two: 8188 entries 5.2 / 7.8
-// us, 16384 entries 6.7 / 8.7, 32768 entries 10.9 / 8.4.
+// entry, for top-k of 1, 2, 4 or 8.  Measured on MI355X, layouts back to back, one kernel against
+// two: 8188 entries 5.2 / 7.8 us, 16384 entries 6.7 / 8.7, 32768 entries 10.9 / 8.4.
+// Other k stop at one tile (4096 entries; 2048 above 512 experts).  There the one workgroup that
+// checks the routing ends the kernel, the sooner the longer the rows are that a thread cannot
+// hold; one kernel of 16-wave workgroups against two: top-24 of 128 experts 5000 entries 6.6 / 10.2
+// us, 8000 8.9 / 10.3, 12000 11.8 / 10.4; top-64 8000 7.5 / 9.7, 12000 9.6 / 9.7.  So the line
+// could lie at 8000 entries for these, and for top-3 to 7 as high as for top-8 (top-6 of 64
+// experts, 4-wave workgroups: 8000 entries 5.4 / 8.4, 20000 8.1 / 8.5).
 constexpr int64_t kLayoutOneKernelIds = 20480;
 // Rank workgroups aimed at over all tiles (one per compute unit), of 4 waves, or 16 above
 // kLayoutWideRank entries where a tile still has several workgroups.  Each reads the whole

@@ -106,15 +106,6 @@ __device__ __forceinline__ bool same_id(const LayoutArgs &a, int x, int y) {
     return x == y && (unsigned)x < (unsigned)a.all_E;
 }
 
-// Does entry i (id) repeat an expert named by an earlier slot of its token row?
-__device__ __forceinline__ bool repeats_before(const LayoutArgs &a, uint32_t i, int id) {
-    const int j = (int)(i - a.k_div.div(i) * a.k_div.d);
-    bool dup = false;
-    for (int d = 1; d <= j; ++d)
-        dup |= same_id(a, id, a.topk_idx[(int64_t)i - d]);
-    return dup;
-}
-
 // Does any expert appear twice among the N ids of a token row?  (Ids outside [0, E) are
 // errors of their own; the equality of the raw ids is tested first, rows that pass it are
 // rare.)
@@ -141,7 +132,7 @@ __device__ __forceinline__ bool row_repeats(const LayoutArgs &a, const int (&id)
 //   each E + 1 bins of hist_copies(E) counters in LDS, zeroed by the caller; bin E takes the
 //   ids outside the window (no branch per id).
 // CHECK: ORs their routing errors into err.  K: top-k when it is 1, 2, 4 or 8 (whole token
-//   rows in a thread's groups; 8 with PAIRS), else 0.
+//   rows in a thread's groups; 8 with PAIRS), else 0 (repeated experts: check_rows).
 // begin and split are multiples of 64, end too unless it is the array's.  ids: the first
 // batch.
 template <int K, bool PAIRS, bool COUNT, bool CHECK>
@@ -180,9 +171,6 @@ __device__ __forceinline__ void visit_ids(const LayoutArgs &a, uint32_t begin, u
                     const i32x4 u = ids.v[b - b % 2];
                     dup |= row_repeats<8>(a, {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]});
                 }
-                if (K == 0)
-                    for (int c = 0; c < 4; ++c)
-                        dup |= repeats_before(a, 4 * g + c, v[c]);
             }
             int *hist = 4 * g < split ? hist_pre : hist_all;
 #pragma unroll
@@ -194,13 +182,104 @@ __device__ __forceinline__ void visit_ids(const LayoutArgs &a, uint32_t begin, u
     const uint32_t i = full * 4 + tid;  // the last 0..3 entries of the array
     if (i < end) {
         const int id = a.topk_idx[i];
-        if (CHECK && K != 1)
-            dup |= repeats_before(a, i, id);
+        if (CHECK && K == 2 && tid == 0)
+            dup |= same_id(a, id, a.topk_idx[i + 1]);  // an odd number of rows ends with one
         visit(id, true, i < split ? hist_pre : hist_all);
     }
     if (CHECK)
         err |= (bad ? kRoutingIdOutOfRange : 0u) | (dup ? kRoutingDuplicate : 0u);
 }
+
+// Routing check of general rows (K = 0): whether a token row that starts in [begin, end) names
+// an expert twice (its last ids may lie past end: the array holds whole rows).  Three ways,
+// whose cost per id hardly grows with k:
+//   k < 8     a thread holds a row;
+//   k <= 64   a wave holds as many whole rows as it has lanes for, finds the lanes with equal
+//             ids by ballots and keeps those of its own row;
+//   longer    a wave marks a row's experts in a bitmap (`seen`: an LDS word per thread).
+// Measured on MI355X, whole layouts of 128 experts, against comparing each id with the row's
+// earlier ones, loaded again: 4000 entries of top-16 6.2 us (10.9), top-32 6.2 (24.5), top-64 6.2
+// (38.1), top-96 6.2 (52.9); 400000 entries of top-16 16.0 (22.7), top-64 16.3 (58.0), top-96 15.1
+// (79.7); of 64 experts, top-6 12.3 (15.0), top-7 12.5 (16.0), where ballots take 14.4.
+template <int N>
+__device__ __forceinline__ bool rows_repeat(const LayoutArgs &a, uint32_t row, uint32_t row_end, uint32_t step) {
+    bool dup = false;
+    for (; row < row_end; row += step) {
+        int id[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            id[j] = a.topk_idx[row * N + j];
+        dup |= row_repeats<N>(a, id);
+    }
+    return dup;
+}
+constexpr int kCheckBatch = 4;  // id loads in flight per lane
+__device__ __forceinline__ bool rows_repeat_ballots(const LayoutArgs &a, uint32_t begin_row, uint32_t row_end, int tid,
+                                                    int threads) {
+    const int lane = tid & (kWave - 1);
+    const uint32_t k = a.k_div.d, rows = kWave / k;  // whole rows of a wave
+    const uint32_t mine = a.k_div.div(lane), slot = lane - mine * k, step = threads / kWave * rows;
+    const uint64_t row_lanes = (k == kWave ? ~0ull : (1ull << k) - 1) << (lane - slot);
+    const int bits = a.all_E > 1 ? 32 - __builtin_clz(a.all_E - 1) : 0;
+    bool dup = false;
+    for (uint32_t r = begin_row + tid / kWave * rows; r < row_end; r += kCheckBatch * step) {  // wave-uniform
+        int id[kCheckBatch];
+#pragma unroll
+        for (int b = 0; b < kCheckBatch; ++b) {
+            const uint32_t row = r + b * step + mine;
+            id[b] = mine < rows && row < row_end ? a.topk_idx[row * k + slot] : -1;
+        }
+#pragma unroll
+        for (int b = 0; b < kCheckBatch; ++b) {
+            if (r + b * step >= row_end)
+                break;
+            const bool ok = (unsigned)id[b] < (unsigned)a.all_E;
+            dup |= ok && __popcll(match_expert(id[b], ok, bits) & row_lanes) > 1;
+        }
+    }
+    return dup;
+}
+__device__ __forceinline__ bool rows_repeat_bitmap(const LayoutArgs &a, uint32_t begin_row, uint32_t row_end, int tid,
+                                                   int threads, uint32_t *seen) {
+    const int lane = tid & (kWave - 1);
+    const uint32_t k = a.k_div.d;
+    uint32_t *map = seen + (tid & ~(kWave - 1));  // this wave's
+    bool dup = false;
+    for (uint32_t r = begin_row + tid / kWave; r < row_end; r += threads / kWave) {  // wave-uniform
+        map[lane] = 0;
+        __builtin_amdgcn_wave_barrier();  // a wave's LDS operations complete in order
+        const int32_t *ids = a.topk_idx + r * k;
+        int next = ids[lane];
+        for (uint32_t c = lane; c - lane < k; c += kWave) {
+            const int id = next;
+            next = c + kWave < k ? ids[c + kWave] : -1;
+            if ((unsigned)id < (unsigned)a.all_E)
+                dup |= (atomicOr(&map[id / 32], 1u << (id % 32)) >> (id % 32)) & 1u;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    return dup;
+}
+__device__ __forceinline__ bool check_rows(const LayoutArgs &a, uint32_t begin, uint32_t end, int tid, int threads,
+                                           uint32_t *seen) {
+    const uint32_t k = a.k_div.d;
+    auto first_row = [&](uint32_t entry) {  // of the rows that start at `entry` or later
+        const uint32_t q = a.k_div.div(entry);
+        return q + (q * k != entry ? 1u : 0u);
+    };
+    const uint32_t r0 = first_row(begin), r1 = first_row(end);
+    switch (k) {
+    case 3: return rows_repeat<3>(a, r0 + tid, r1, threads);
+    case 5: return rows_repeat<5>(a, r0 + tid, r1, threads);
+    case 6: return rows_repeat<6>(a, r0 + tid, r1, threads);
+    case 7: return rows_repeat<7>(a, r0 + tid, r1, threads);
+    }
+    return k <= kWave ? rows_repeat_ballots(a, r0, r1, tid, threads)
+                      : rows_repeat_bitmap(a, r0, r1, tid, threads, seen);
+}
+// LDS words of `seen`.
+__host__ __device__ constexpr int seen_ints(int k, int threads) { return k > kWave ? threads : 0; }
+static_assert(kMaxExperts <= 32 * kWave, "a wave's bitmap holds every expert");
 
 // ORs the workgroup's routing errors into the LDS word *flags.
 __device__ __forceinline__ void gather_errors(uint32_t err, int lane, int *flags) {
@@ -398,7 +477,7 @@ __device__ __forceinline__ void sum_columns(const LayoutArgs &a, int tiles, int 
 // Count kernel: the tile's counts and error bits, for the rank kernel.
 template <int K>
 __global__ __launch_bounds__(1024) void layout_count_kernel(LayoutArgs a, uint32_t tile_entries) {
-    extern __shared__ __align__(16) int hist[];  // E + 1 bins of counters, then the error bits
+    extern __shared__ __align__(16) int hist[];  // E + 1 bins of counters, the error bits, check_rows' words
     const int tid = threadIdx.x, threads = blockDim.x, E = a.E;
     const int words = hist_copies(E) * (E + 1);
     const uint32_t begin = blockIdx.x * tile_entries, end = min(begin + tile_entries, (uint32_t)a.slots);
@@ -409,6 +488,8 @@ __global__ __launch_bounds__(1024) void layout_count_kernel(LayoutArgs a, uint32
     __syncthreads();
     uint32_t err = 0;
     visit_ids<K, K == 8, true, true>(a, begin, end, 0, tid, threads, hist, hist, err, ids);
+    if (K == 0 && check_rows(a, begin, end, tid, threads, reinterpret_cast<uint32_t *>(hist) + words + 1))
+        err |= kRoutingDuplicate;
     gather_errors(err, tid & (kWave - 1), &hist[words]);
     __syncthreads();
     for (int e = tid; e < E; e += threads)
@@ -451,6 +532,8 @@ __global__ __launch_bounds__(W * 64) void layout_rank_kernel(LayoutArgs a, uint3
         __syncthreads();
         first_batch<K == 8>(a, 0, n, tid, kThreads, batch);
         visit_ids<K, K == 8, false, true>(a, 0, n, 0, tid, kThreads, nullptr, nullptr, err, batch);
+        if (K == 0 && check_rows(a, 0, n, tid, kThreads, reinterpret_cast<uint32_t *>(lds) + 1))
+            err |= kRoutingDuplicate;
         gather_errors(err, lane, flags);
         __syncthreads();
         if (tid == 0)
@@ -557,8 +640,9 @@ template <int W, int K>
 void launch_one(const LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
     constexpr int kThreads = W * kWave;
     const unsigned runs = (unsigned)std::max<int64_t>(1, (a.slots + kThreads - 1) / kThreads);
+    const size_t check_lds = sizeof(int) * (1 + (size_t)seen_ints(a.k, kThreads));
     hipExtLaunchKernelGGL((layout_rank_kernel<W, true, K>), dim3(runs + 1), dim3(kThreads),
-                          (uint32_t)rank_lds_bytes<W, true>(a.E), stream, ts.start, ts.stop, 0, a,
+                          (uint32_t)std::max(rank_lds_bytes<W, true>(a.E), check_lds), stream, ts.start, ts.stop, 0, a,
                           (uint32_t)a.slots, 1);
 }
 
@@ -574,7 +658,8 @@ void launch_layout_k(LayoutArgs &a, hipStream_t stream, TraceSlot ts) {
     a.e4_div = fast_div((uint32_t)std::max(1, a.E / 4));
     const int64_t tile_entries = (int64_t)g.waves * kWave * g.rounds;
     const unsigned count_threads = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(256, tile_entries / 8 / kWave * kWave));
-    const size_t count_lds = sizeof(int) * ((size_t)hist_copies(a.E) * (a.E + 1) + 1);
+    const size_t count_lds =
+        sizeof(int) * ((size_t)hist_copies(a.E) * (a.E + 1) + 1 + seen_ints(a.k, (int)count_threads));
     // both kernels inside one pair of timing events: the layout's time
     hipExtLaunchKernelGGL((layout_count_kernel<K>), dim3((unsigned)g.tiles), dim3(count_threads), (uint32_t)count_lds,
                           stream, ts.start, nullptr, 0, a, (uint32_t)tile_entries);

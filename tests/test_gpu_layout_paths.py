@@ -68,3 +68,53 @@ def test_bad_routing_is_found(T, E, k, row):
     lay = ep.dispatch_layout(device(twice, False), E, 1)
     torch.cuda.synchronize()
     assert int(lay.workspace[:4].view(torch.int32)) == 1
+
+
+@pytest.mark.parametrize("T,E,k", [(1366, 60, 3), (8003, 250, 7), (1301, 130, 63), (700, 2048, 64), (1000, 96, 65),
+                                   (90, 700, 130), (40001, 33, 3)])
+def test_general_rows_are_checked_wherever_they_lie(T, E, k):
+    """Top-k without rows in registers: a repeated expert is found in rows that two tiles share,
+    at both ends of a wave's rows and in any two slots; equal slots of two rows are no repeat."""
+    idx = routing("random", T, E, k, seed=11)
+    idx[1::7] = idx[0]  # neighbouring rows with the same experts
+    clean = ep.dispatch_layout(device(idx, False), E, 1)
+    ep.layout_validate(clean)
+    per_wave = max(1, 64 // k)
+    rows = {0, 1, per_wave - 1, per_wave, T // 2, T - 1}
+    rows |= {entry // k for entry in range(1024, T * k, 1024)}  # tiles end at multiples of 1024 (or of 256)
+    rng = np.random.default_rng(k)
+    for row in sorted(r for r in rows if r < T)[:48]:
+        a, b = sorted(rng.choice(k, 2, replace=False))
+        bad = idx.copy()
+        bad[row, b] = bad[row, a]
+        say(f"repeat in slots {a}, {b} of row {row}: T={T} E={E} k={k}")
+        lay = ep.dispatch_layout(device(bad, False), E, 1)
+        torch.cuda.synchronize()
+        assert int(lay.workspace[:4].view(torch.int32)) == 2, row
+        if E > 300:
+            local = ep.dispatch_layout_local(device(bad, False), E, 5, 9)
+            torch.cuda.synchronize()
+            assert int(local.workspace[:4].view(torch.int32)) == 2, row
+
+
+def test_a_long_row_costs_no_more_per_id_than_a_short_one():
+    """The layout of 400000 entries in rows of 64 ids takes at most twice that in rows of 8 (16 and
+    14 us; a check that reloads every earlier id of a row makes it 58)."""
+    us = {}
+    for k in (8, 64):
+        T, E = 400000 // k, 128
+        table = routing("random", 512, E, k, seed=k)
+        idx = device(table[np.random.default_rng(k).integers(0, 512, T)], False)
+        lay = ep.dispatch_layout(idx, E, 1)
+        say(f"layout time T={T} E={E} k={k}")
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(100):
+                ep.dispatch_layout(idx, E, 1, out=lay)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 10)
+        us[k] = min(times)
+    assert us[64] <= 2 * us[8], us
