@@ -24,18 +24,25 @@
 //   D. wave 0 ranks the workgroup's own entries in flat order (ballot match-any and a
 //      masked popcount, as the layout kernel does: stable), stores slot_pos / row_src and
 //      keeps the rows in LDS;
-//   E. each wave stores its tokens' rows (or its part of one) to their k packed rows
-//      (non-temporal; U groups of 64 16-byte vectors, one per lane, all loads in flight
-//      together; loads cached: rows the caller has just written, or reads again, are found
-//      in the memory-side cache).
+//   E. each wave stores its tokens' rows (or its part of one) to their k packed rows (loads
+//      and stores non-temporal; U groups of 64 16-byte vectors, one per lane, all loads in
+//      flight together).  For k <= 2 the workgroup's rows are all in before it stores.
 // One more workgroup checks the routing (an id outside [0,E), an expert twice in one token
 // row) and stores the status word: in every workgroup beside the counting, with the 16
 // copies as rows of counters in one LDS bank, the kernel took 9.0 us at 256 tokens, top-8 of
 // 256 experts, 14 KiB rows (now 7.4), 20.4 at 2048 tokens, top-8 of 128, 4 KiB rows (16.7), 12.6
-// at 8192 tokens, top-2 of 256, 1 KiB rows (8.6).  Cached against non-temporal row loads, the
-// 4096-token, top-2 layer of 8 KiB rows: 32.6 against 35.6 us where part of the rows is still
-// in the memory-side cache, 36.6 against 35.5 where none is (the combine after it 17.2 against
-// 16.0); cached, since a program packs rows that it has just written.
+// at 8192 tokens, top-2 of 256, 1 KiB rows (8.6).
+// Row loads: cached ones are found again only by a program that packs the same rows twice
+// without writing them (8192 tokens, top-1 of 4 KiB rows: 23.6 us a layer against 26.6).  Where
+// the rows have just been written, or are in no cache, they make the combine after the dispatch
+// slower; written, packed and combined, cached / non-temporal: 1024 tokens, top-1 of 8 KiB rows 13.1
+// / 12.2 us, 4096 tokens, top-2 of 8 KiB 44.8 / 43.4, 16384 tokens, top-1 of 8 KiB 148 / 134, 2048
+// tokens, top-8 of 4 KiB 35.0 / 34.9.
+// Rows in before stores (k <= 2, where reads are a third to a half of the traffic): the
+// counting takes less time than the device's row loads, so a workgroup that stores at once
+// mixes its writes with the others' reads.  Without / with the wait, layers with rows in no
+// cache: 4096 tokens, top-2 of 8 KiB 34.6 / 33.7 us, top-1 of 256 experts 25.1 / 23.2, 1024 tokens,
+// top-1 of 8 KiB 9.6 / 9.3; for more slots it is slower (1024 tokens, top-4 of 14 KiB 26.6 / 27.1).
 // The outputs equal those of the layout kernel followed by the pack kernel, bit for bit.
 // Workgroups never wait on each other, so nothing needs them resident together.
 //
@@ -213,7 +220,7 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
         const u32x4 *src = x + min(wtok, tok1 - 1) * V + col + lane;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            d[u] = src[u * kWave];
+            d[u] = __builtin_nontemporal_load(src + u * kWave);
     }
     for (int i = tid; i < kHist / 4; i += threads) {
         reinterpret_cast<i32x4 *>(s_rest)[i] = i32x4{0, 0, 0, 0};
@@ -365,6 +372,8 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
             }
         }
     }
+    if (K <= 2)
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's row is in
     __syncthreads();
 
     // E. store each token row (this wave's part of it) to its k packed rows
@@ -377,7 +386,7 @@ __global__ __launch_bounds__(kFMaxThreads) void layout_pack_kernel(FusedArgs a, 
             const u32x4 *src = x + t * V + col + lane;
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                d[u] = src[u * kWave];
+                d[u] = __builtin_nontemporal_load(src + u * kWave);
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -442,7 +451,10 @@ hipError_t launch_k(const FusedArgs &a, int32_t tpw, int32_t split, unsigned blo
 // rows measured on MI355X, 256 experts top-8, 14 KiB rows: 256 tokens 9.8 against 11.4 us,
 // 512 tokens 16.1 against 16.9 us.  Otherwise 4, 8 or 16 waves by the entries (4 or 8
 // win up to 8192 entries, 16 above), with tpw tokens per wave so that the workgroups hold
-// at most kFMaxWaves waves.
+// at most kFMaxWaves waves.  Top-1 takes 8 waves once they still give every compute unit a
+// workgroup: more rows are then in before a store (4096 tokens of 8 KiB rows, layers with 4 / 8
+// waves 24.4 / 23.7 us, fresh rows the same; 2048 tokens 14.2 / 14.2, fresh rows 19.4 / 19.2; 1024
+// tokens 9.3 / 9.8).
 struct FusedGeom {
     int32_t split = 1, waves = 4, tpw = 1;
     int64_t blocks = 0;
@@ -476,7 +488,7 @@ FusedGeom fused_geometry(int64_t T, int32_t k, int G) {
             }
         }
     }
-    g.waves = slots <= 4096 ? 4 : (slots <= 8192 ? 8 : 16);
+    g.waves = (k == 1 ? slots < 8 * 256 : slots <= 4096) ? 4 : (slots <= 8192 ? 8 : 16);
     const int64_t max_blocks = kFMaxWaves / g.waves;
     const int64_t per_block_min = (T + max_blocks - 1) / max_blocks;
     g.tpw = (int32_t)((per_block_min + g.waves - 1) / g.waves);

@@ -97,6 +97,10 @@ FUSED_CASES = [
     ("split_tokens_1023", 1023, 1024, 8, 2, 4, "random"),
     ("split_k1_four_tokens_per_group", 300, 2048, 16, 1, 4, "random"),  # m*k kept a multiple of 4
     ("split_tokens_1024", 1024, 1024, 8, 2, 4, "random"),
+    # top-1: 4-wave workgroups below 2048 tokens, 8-wave ones from there up
+    ("k1_tokens_2047", 2047, 512, 8, 1, 2, "random"),
+    ("k1_tokens_2048", 2048, 512, 8, 1, 2, "random"),
+    ("k2_under_120_mib_packed", 7679, 4096, 8, 2, 4, "skewed"),
 ]
 
 
@@ -171,6 +175,7 @@ FALLBACK_CASES = [
     ("rows12", 200, 6144, 16, 2, 4),
     ("h520_not_whole_groups", 100, 520, 8, 2, 2),
     ("slots_over_limit", 40000, 512, 8, 2, 4),
+    ("k2_120_mib_packed", 7680, 4096, 8, 2, 4),
 ]
 
 
