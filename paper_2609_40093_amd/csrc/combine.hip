@@ -192,6 +192,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ r
 // 144.8, 42 MiB (top-2 of 8 KiB) 50.5 / 50.6, 47 MiB (top-8 of 14 KiB) 180 / 167.7, 50 MiB (top-2
 // of 8 KiB) 65.5 / 58.4, 57 MiB (top-8 of 14 KiB) 211 / 191 (the pack 112 / 92).
 constexpr int64_t kCombineWriteThroughBelow = 44ll << 20;
+// After the one-kernel dispatch, whose row loads are non-temporal, the line lies higher for bf16
+// results.  Write-through / non-temporal, rows in no cache: top-2 of 14 KiB rows 47 MiB 49.9 / 53.0
+// us, 56 MiB 59.8 / 64.1; of 8 KiB 59 MiB 64.5 / 69.1; of 4 KiB 50 MiB 58.6 / 61.9; top-1 of 14 KiB 56
+// MiB 39.1 / 43.4, of 8 KiB 59 MiB 42.6 / 47.1, 82 MiB 58.8 / 65.5; with the rows just written, top-2
+// 56 MiB 74.9 / 78.5, top-1 82 MiB 85.5 / 83.3, 93 MiB 100 / 92.
+constexpr int64_t kFusedWriteThroughBelow = 88ll << 20;
+inline int64_t write_through_below(Slots expect, bool out_f32) {
+    return expect == Slots::kFused && !out_f32 ? kFusedWriteThroughBelow : kCombineWriteThroughBelow;
+}
 // From 128 MiB of output up the combine runs as several launches over consecutive token
 // ranges of about 64 MiB of output each (measured on MI355X, top-8 of 14 KiB rows, 32K
 // tokens, non-temporal stores: one launch 747 us, 2 / 4 / 8 / 16 / 32 / 64 launches 733 /
@@ -223,7 +232,7 @@ uint32_t reserved_lds(int32_t k, int loads_512) {
 }
 
 struct CombineCall {
-    bool all_rows;  // every slot is expected to have a row
+    Slots expect;
     const void *recv;
     const int32_t *slot_pos;
     const float *topk_w;
@@ -251,8 +260,8 @@ hipError_t launch_ranges(const CombineCall &c, hipStream_t stream) {
     const int64_t per = std::min<int64_t>((c.T + launches - 1) / launches, (INT32_MAX - kWaves) / chunks.d);
     if (per < 1)
         return hipErrorInvalidValue;
-    const bool wt = out_bytes < kCombineWriteThroughBelow;
-    const uint32_t lds = c.all_rows && !wt ? reserved_lds(c.k, (F32_OUT ? 1 : 2) * U * KC) : 0;
+    const bool wt = out_bytes < write_through_below(c.expect, F32_OUT);
+    const uint32_t lds = c.expect != Slots::kSome && !wt ? reserved_lds(c.k, (F32_OUT ? 1 : 2) * U * KC) : 0;
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
     const TraceSlot ts = trace_acquire();  // one pair of events around every launch of the call
     for (int64_t t0 = 0; t0 < c.T; t0 += per) {
@@ -415,10 +424,10 @@ __global__ __launch_bounds__(256) void accumulate_kernel(const u32x4 *__restrict
 
 hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float *topk_w,
                           int64_t T, int32_t H, int32_t k, void *out, bool out_f32,
-                          int64_t max_rows, hipStream_t stream, bool all_rows, RoundSel sel) {
+                          int64_t max_rows, hipStream_t stream, Slots expect, RoundSel sel) {
     if (T == 0)
         return hipSuccess;
-    const CombineCall c{all_rows, recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
+    const CombineCall c{expect, recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
     if (sel.round)  // graph-replayed rounds: the general instance reading the round
         return out_f32 ? launch_ranges<4, 8, true, false, false, true>(c, stream)
                        : launch_ranges<2, 8, false, false, false, true>(c, stream);

@@ -310,7 +310,7 @@ extern "C" ep_status ep_combine_rows(const void *y_dev, int64_t max_rows, const 
                            (max_rows > 0 && (!y_dev || !aligned16(y_dev)))))
         return fail(EP_ERR_INVALID_ARG, "ep_combine_rows: slot_pos, topk_w and 16-byte aligned y/out are required");
     EP_HIP(ep::launch_combine(y_dev, slot_pos, topk_w, num_tokens, hidden, topk, out_dev, out_dtype == EP_OUT_F32,
-                              max_rows, stream, /*all_rows=*/false));
+                              max_rows, stream, ep::Slots::kSome));
     return EP_OK;
 }
 
@@ -765,6 +765,7 @@ extern "C" ep_status ep_dispatch(const void *x_dev, int64_t num_tokens, int32_t 
     }
     EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, s->dev_send[buf], s->max_rows,
                            pinned ? s->epoch_word(buf) : nullptr, epoch, stream));
+    s->fused[buf] = false;
     if (!pinned || rows == 0)
         return EP_OK;
     if (exchange)
@@ -822,6 +823,7 @@ extern "C" ep_status ep_dispatch_fused(const int32_t *topk_idx, int64_t num_toke
     a.epoch_word = pinned ? s->epoch_word(buf) : nullptr;
     a.epoch = epoch;
     EP_HIP(ep::launch_layout_pack(a, stream));
+    s->fused[buf] = true;
     if (!pinned)
         return EP_OK;
     return dispatch_default_legs(s, buf, epoch, T * k, stream);
@@ -879,7 +881,8 @@ extern "C" ep_status ep_combine(ep_staging *s, int32_t buf, uint32_t epoch, cons
         EP_HIP(hipMemcpyAsync(s->dev_recv[buf], s->host_recv[buf], (size_t)bytes, hipMemcpyHostToDevice, stream));
     }
     EP_HIP(ep::launch_combine(s->dev_recv[buf], slot_pos, topk_w, num_tokens, hidden, topk, out_dev,
-                              out_dtype == EP_OUT_F32, s->max_rows, stream, /*all_rows=*/true));
+                              out_dtype == EP_OUT_F32, s->max_rows, stream,
+                              s->fused[buf] ? ep::Slots::kFused : ep::Slots::kPacked));
     return EP_OK;
 }
 
@@ -1024,7 +1027,7 @@ extern "C" ep_status ep_combine_graph(ep_staging *s, const int32_t *slot_pos, co
     sel.alt = src[1];
     sel.round = s->dev_round;
     EP_HIP(ep::launch_combine(src[0], slot_pos, topk_w, num_tokens, hidden, topk, out_dev, out_dtype == EP_OUT_F32,
-                              s->max_rows, stream, /*all_rows=*/false, sel));
+                              s->max_rows, stream, ep::Slots::kSome, sel));
     // the returned rows of this round are consumed: credit the buffer set to the senders
     EP_HIP(ep::launch_round_stamp(s->dev_round, s->recv_credit(0), 1, 1, stream));
     return EP_OK;

@@ -227,11 +227,15 @@ hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int
                        void *packed, int64_t max_rows, uint32_t *epoch_word, uint32_t epoch,
                        hipStream_t stream, RoundSel sel = {}, bool fence_system = false);
 
-// all_rows: every slot is expected to have a row (a whole layout's; any slot may lack one
-// all the same), which decides how many workgroups run at once.
+// What the combine's launch may expect of its slots; no result depends on it.
+enum class Slots {
+    kSome,    // any may lack a row (a window layout, a caller's own positions)
+    kPacked,  // every slot has a row; the pack kernel dispatched them
+    kFused,   // every slot has a row; the one-kernel dispatch did
+};
 hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float *topk_w,
                           int64_t T, int32_t H, int32_t k, void *out, bool out_f32,
-                          int64_t max_rows, hipStream_t stream, bool all_rows, RoundSel sel = {});
+                          int64_t max_rows, hipStream_t stream, Slots expect, RoundSel sel = {});
 
 // Per-sender accumulation (combine.hip, signal.hip).  masks: device words, masks[0] the
 // senders whose rows need no wait, masks[i + 1] the senders landed before pass i.

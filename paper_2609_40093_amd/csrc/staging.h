@@ -116,6 +116,7 @@ struct ep_staging {
     hipStream_t up = nullptr, down = nullptr;
     hipEvent_t ev_up_in[ep::kMaxBuffers] = {}, ev_up_done[ep::kMaxBuffers] = {};
     hipEvent_t ev_down_in[ep::kMaxBuffers] = {}, ev_down_done[ep::kMaxBuffers] = {};
+    bool fused[ep::kMaxBuffers] = {};  // the set's last dispatch was the one kernel (combine's store policy)
     int64_t timeout_us = 10ll * 1000 * 1000;
     int32_t sleep_units = 2;
     int64_t wall_clock_khz = 100000;

@@ -45,3 +45,37 @@ def test_slots_without_rows(k, H):
         assert (np.abs(got - exact) <= bound + extra * (np.abs(exact) + bound)).all()
         empty = ~has.any(axis=1)
         assert not out.view(torch.int32 if dt == torch.float32 else torch.int16).cpu().numpy()[empty].any()
+
+
+@pytest.mark.parametrize("H,dtype", [(7168, torch.bfloat16), (3584, torch.float32)])
+def test_store_policies_agree(H, dtype):
+    """The combine stores by its output's bytes and by how its rows were dispatched (one kernel,
+    two, a caller's own positions): 56 MiB of output, the same bits each way."""
+    T, E, k, R = 4096, 64, 2, 4
+    gen = torch.Generator(device=DEV).manual_seed(H)
+    idx = torch.rand((T, E), device=DEV, generator=gen).topk(k, dim=1).indices.to(torch.int32)
+    w = torch.rand((T, k), device=DEV, generator=gen)
+    x = torch.randint(-2**15, 2**15, (T, H), device=DEV, dtype=torch.int16, generator=gen)
+    y = torch.empty((T * k, H), device=DEV, dtype=torch.bfloat16).normal_(generator=gen)
+    st = ep.Staging("hbm", T * k, H, R, num_buffers=2)
+    outs = []
+    for buf, one in ((0, True), (1, False), (1, True), (0, False)):
+        say(f"combine after a dispatch in {'one kernel' if one else 'two'}: buffer {buf} H={H} {dtype}")
+        if one:
+            lay = ep.dispatch_fused(x, idx, E, R, st, buf=buf, epoch=1)
+        else:
+            lay = ep.dispatch_layout(idx, E, R)
+            ep.dispatch(x, lay.slot_pos, st, topk=k, buf=buf, epoch=1, rank_offsets=lay.rank_offsets)
+        assert torch.equal(ep.pack(x, lay.slot_pos, torch.empty_like(y.view(torch.int16)), topk=k),
+                           st.read_device("send", T * k, buf=buf))
+        st.write_device("recv", y.view(torch.int16), buf=buf)
+        outs.append(ep.combine(st, lay.slot_pos, w, out=torch.empty((T, H), dtype=dtype, device=DEV), buf=buf, epoch=1))
+    outs.append(ep.combine_rows(y, lay.slot_pos, w, torch.empty((T, H), dtype=dtype, device=DEV)))
+    terms = w.double()[:, :, None] * y[lay.slot_pos.long()].view(T, k, H).double()
+    exact, bound = terms.sum(dim=1), (k + 1) * 2.0**-24 * terms.abs().sum(dim=1)
+    if dtype == torch.bfloat16:
+        bound = bound + 2.0**-8 * (exact.abs() + bound)
+    assert (outs[0].double() - exact).abs().le(bound).all()
+    for out in outs[1:]:
+        assert torch.equal(out, outs[0])
+    st.close()
