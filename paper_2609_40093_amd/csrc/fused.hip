@@ -51,8 +51,8 @@
 // top-8), T*k <= 65536 for E <= 64 and k <= 4, else T*k <= 16384 for rows up to 8 KiB and
 // 8192 for longer ones (every workgroup reads and counts every id before its stores:
 // beyond that the layout kernel's exchange of totals costs less), rows of 1, 2, 4, 8, 14
-// or 16 groups (H = 512 * groups), under 120 MiB packed for k >= 2, a 16-byte aligned routing
-// array.  The split runs of fewer than 1024 tokens keep the same limits.
+// or 16 groups (H = 512 * groups), under 136 MiB packed for k = 2 and under 120 for k = 4 and 8,
+// a 16-byte aligned routing array.  The split runs of fewer than 1024 tokens keep the same limits.
 #include "ep_internal.h"
 #include "wave.h"
 
@@ -67,11 +67,15 @@ constexpr int64_t kFMaxSlots = 65536;        // T*k: every workgroup reads every
 // with 4 KiB rows, 20-24 against 23-29 us, and loses with 14 KiB rows, 56 against 55 us)
 constexpr int64_t kFMaxSlotsWide = 16384;    // rows of at most 8 KiB
 constexpr int64_t kFMaxSlotsWideLong = 8192; // longer rows
-// Bytes packed from which the two steps as their own kernels win for k >= 2 (their pack gives
-// every slot its own wave; measured on MI355X, whole passes, one kernel / two: 64 MiB, top-8
-// of 4 KiB rows 29.9 / 34.9 us; 112 MiB, top-8 of 14 KiB 50.6 / 52.6; 128 MiB, top-2 of 8 KiB
-// 73.7 / 70.0, top-4 of 4 KiB 64.1 / 61.2)
-constexpr int64_t kFMaxBytes = 120ll << 20;
+// Bytes packed from which the two steps as their own kernels win (their pack gives every slot
+// its own wave).  Measured on MI355X, whole passes, one kernel / two.  k >= 4: 64 MiB, top-8 of 4
+// KiB rows 29.9 / 34.9 us; 112 MiB, top-8 of 14 KiB 50.6 / 52.6; 128 MiB, top-4 of 4 KiB 64.4 / 60.4,
+// of 8 KiB 59.2 / 58.7.  k = 2, rows in no cache, and just written (the pack's cached row loads then
+// cost what they cost the combine here, above): 128 MiB of 8 KiB rows 68.4 / 69.9, 84.6 / 89.9; 137
+// MiB of 14 KiB 75.3 / 73.8, 91.2 / 94.5; 141 MiB of 8 KiB 79.5 / 77.0, 96.1 / 98.6; 160 MiB of 4 KiB
+// 88.5 / 85.4, 111.4 / 109.3; 256 MiB of 4 KiB 153 / 136, 187 / 190; of 8 KiB 151 / 137, 180 / 189.
+// k = 1 has no such limit.
+constexpr int64_t kFMaxBytes = 120ll << 20, kFMaxBytesTop2 = 136ll << 20;
 constexpr int kFMaxOwn = 256;                // entries one workgroup owns (LDS rows)
 constexpr int kFOwnRounds = kFMaxOwn / kWave;
 constexpr int kFBatch = 4;                   // 16-byte id loads in flight per lane
@@ -506,7 +510,7 @@ bool fused_layout_pack_fits(int64_t T, int32_t k, int32_t E, int32_t H, const vo
         return false;
     if (H % 512 != 0)
         return false;
-    if (k > 1 && T * k * (int64_t)H * 2 >= kFMaxBytes)
+    if (k > 1 && T * k * (int64_t)H * 2 >= (k == 2 ? kFMaxBytesTop2 : kFMaxBytes))
         return false;
     const int G = H / 512;
     return (G == 1 || G == 2 || G == 4 || G == 8 || G == 14 || G == 16) &&

@@ -100,7 +100,9 @@ FUSED_CASES = [
     # top-1: 4-wave workgroups below 2048 tokens, 8-wave ones from there up
     ("k1_tokens_2047", 2047, 512, 8, 1, 2, "random"),
     ("k1_tokens_2048", 2048, 512, 8, 1, 2, "random"),
-    ("k2_under_120_mib_packed", 7679, 4096, 8, 2, 4, "skewed"),
+    # under the limits of bytes packed (17406 entries: also the count loop with rows of 8 groups)
+    ("k2_under_136_mib_packed", 8703, 4096, 8, 2, 4, "skewed"),
+    ("k4_under_120_mib_packed", 3839, 4096, 16, 4, 4, "random"),
 ]
 
 
@@ -175,7 +177,8 @@ FALLBACK_CASES = [
     ("rows12", 200, 6144, 16, 2, 4),
     ("h520_not_whole_groups", 100, 520, 8, 2, 2),
     ("slots_over_limit", 40000, 512, 8, 2, 4),
-    ("k2_120_mib_packed", 7680, 4096, 8, 2, 4),
+    ("k2_136_mib_packed", 8704, 4096, 8, 2, 4),
+    ("k4_120_mib_packed", 3840, 4096, 16, 4, 4),
 ]
 
 
