@@ -178,22 +178,20 @@ void launch_chunk(int u, bool partial, dim3 grid, dim3 block, hipStream_t stream
 }
 
 // Store policy of a launch that packs `bytes` bytes of rows of row_bytes, by the time of
-// whole passes (layout, pack, combine; buffers rotated past the memory-side cache), since
-// what a policy leaves in the caches is paid for by the next kernel.  Measured on MI355X,
-// non-temporal / kStoreWT / kStoreWTStream:
+// whole passes (layout, pack, combine), since what a policy leaves in the caches is paid for by
+// the next kernel.  Measured on MI355X, non-temporal / kStoreWT / kStoreWTStream:
 //   rows of whole 64-byte pieces: 52 MiB of 2 KiB rows 33.9 / 38.2 / 33.8 us, 268 MiB of 4 KiB
 //     rows 109.2 / 121.4 / 108.2; of 14 KiB rows 437 MiB 190.6 / 199 / 190.3, 875 MiB 398 / 388 /
 //     391, 1312 MiB 564 / 556 / 553, 2187 MiB 970 / 947 / 960, 3584 MiB 1525 / 1489 / 1484;
-//   other rows, whose ends share a cache line with their neighbours': 17 MiB of 5776 B rows
-//     13.7 / 13.1 / 14.9 us, 35 MiB of 2064 B rows 30.4 / 28.5 / 33.8, 93 MiB of 8208 B rows 54 /
-//     71 / 62, 875 MiB of 14352 B rows 435 / 520 / 484, 2189 MiB 1069 / 1330 / 1195.
+//   other rows, whose ends share a cache line with their neighbours': non-temporal at any size.
+//     93 MiB of 8208 B rows 54 / 71 / 62; 875 MiB of 14352 B rows 435 / 520 / 484, 2189 MiB 1069 / 1330
+//     / 1195; 17 MiB of 5776 B rows (500 tokens, top-6) in no cache 16.4 / 18.9 / 16.9, just written
+//     18.7 / 20.7 / 19.2, 25 MiB of 2064 B rows (4001, top-3) 23.7 / 29.1 / 24.9.  Write-through is
+//     ahead only where a program packs into the same buffers again at once (14.0 against 14.9, 20.9
+//     against 22.5).
 // Rows to host memory (graph rounds) go non-temporal.
 int pack_policy(int64_t bytes, int64_t row_bytes, bool to_host) {
-    if (to_host)
-        return kStoreNT;
-    if (row_bytes % 64 != 0)
-        return bytes < (40ll << 20) ? kStoreWT : kStoreNT;
-    return bytes < (128ll << 20) ? kStoreNT : kStoreWTStream;
+    return to_host || row_bytes % 64 != 0 || bytes < (128ll << 20) ? kStoreNT : kStoreWTStream;
 }
 
 }  // namespace
@@ -249,9 +247,7 @@ hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int
         TraceSlot part;
         part.start = t0 == 0 ? ts.start : nullptr;
         part.stop = t0 + a.T == T ? ts.stop : nullptr;
-        if (policy == kStoreWT)
-            launch_chunk<kStoreWT>(u, V % kWave != 0, grid, block, stream, part, p, a);
-        else if (policy == kStoreWTStream)
+        if (policy == kStoreWTStream)
             launch_chunk<kStoreWTStream>(u, V % kWave != 0, grid, block, stream, part, p, a);
         else
             launch_chunk<kStoreNT>(u, V % kWave != 0, grid, block, stream, part, p, a);
