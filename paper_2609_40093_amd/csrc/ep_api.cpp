@@ -294,7 +294,8 @@ extern "C" ep_status ep_pack(const void *x_dev, int64_t num_tokens, int32_t hidd
         return fail(EP_ERR_INVALID_ARG, "ep_pack: need N >= 0, k >= 1, H a positive multiple of 8, max_rows >= 0");
     if (num_tokens > 0 && (!x_dev || !slot_pos || !out_dev || !aligned16(x_dev) || !aligned16(out_dev)))
         return fail(EP_ERR_INVALID_ARG, "ep_pack: x, slot_pos and a 16-byte aligned out are required");
-    EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, out_dev, max_rows, nullptr, 0, stream));
+    EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, out_dev, max_rows, nullptr, 0, stream,
+                           ep::Slots::kSome));
     return EP_OK;
 }
 
@@ -764,7 +765,7 @@ extern "C" ep_status ep_dispatch(const void *x_dev, int64_t num_tokens, int32_t 
             return st;
     }
     EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, s->dev_send[buf], s->max_rows,
-                           pinned ? s->epoch_word(buf) : nullptr, epoch, stream));
+                           pinned ? s->epoch_word(buf) : nullptr, epoch, stream, ep::Slots::kPacked));
     s->fused[buf] = false;
     if (!pinned || rows == 0)
         return EP_OK;
@@ -991,8 +992,8 @@ extern "C" ep_status ep_dispatch_graph(const void *x_dev, int64_t num_tokens, in
     ep::RoundSel sel;
     sel.alt = dst[1];
     sel.round = s->dev_round;
-    EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, dst[0], s->max_rows, nullptr, 0, stream, sel,
-                           true));
+    EP_HIP(ep::launch_pack(x_dev, num_tokens, hidden, topk, slot_pos, dst[0], s->max_rows, nullptr, 0, stream,
+                           ep::Slots::kPacked, sel, true));
     if (sdma)
         EP_HIP(ep::launch_round_stamp(s->dev_round, s->graph_ready(0), 1, 1, stream));
     else

@@ -220,19 +220,20 @@ struct RoundSel {
     const uint32_t *round = nullptr;
 };
 
+// What a launch may expect of its slots; no result depends on it.
+enum class Slots {
+    kSome,    // any may lack a row (a window layout, a caller's own positions)
+    kPacked,  // every slot has a row; packed by the pack kernel
+    kFused,   // every slot has a row; packed by the one-kernel dispatch
+};
+
 // Also stores `epoch` into *epoch_word (when non-null) for the host leg's flag copies.
 // fence_system: every wave ends with a system-scope release (rows stored to host memory
 // are visible to the host before any later kernel runs).
 hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int32_t *slot_pos,
                        void *packed, int64_t max_rows, uint32_t *epoch_word, uint32_t epoch,
-                       hipStream_t stream, RoundSel sel = {}, bool fence_system = false);
+                       hipStream_t stream, Slots expect, RoundSel sel = {}, bool fence_system = false);
 
-// What the combine's launch may expect of its slots; no result depends on it.
-enum class Slots {
-    kSome,    // any may lack a row (a window layout, a caller's own positions)
-    kPacked,  // every slot has a row; the pack kernel dispatched them
-    kFused,   // every slot has a row; the one-kernel dispatch did
-};
 hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float *topk_w,
                           int64_t T, int32_t H, int32_t k, void *out, bool out_f32,
                           int64_t max_rows, hipStream_t stream, Slots expect, RoundSel sel = {});

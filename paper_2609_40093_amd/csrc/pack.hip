@@ -11,7 +11,8 @@
 // to 16): its loads after the first come from L2 (cached loads), and each wave feeds one
 // write stream instead of k (against one wave storing its chunk k times, MI355X, inputs
 // outside the memory-side cache: 3001 tokens, top-3 of 12 KiB rows 22.1 against 29.5 us, 6.7
-// TB/s; top-2 of 4112 B rows, 4001 tokens 9.3 against 10.7 us).
+// TB/s; top-2 of 4112 B rows, 4001 tokens 9.3 against 10.7 us).  Whole layouts of top-1 and small
+// ones of top-2 take a wave per (token, chunk) instead (pack_token_waves).
 // Rows that are no whole number of 128-byte lines: groups are counted from the line that
 // holds the destination row's start, so that only the row's first and last stores touch
 // partly filled lines, and only those lanes are masked (5003 tokens, top-6 of 5776 B rows:
@@ -19,7 +20,7 @@
 // lines).
 // Chunk: the largest divisor of G of at most 16 groups (16 KiB): a whole row for rows up to
 // 16 KiB; long exact chunks measured faster than 4-group chunks and than 16-group chunks
-// with guarded tails.  Rows with no divisor of at least 4 groups (G a prime above 16) use
+// with guarded tails.  Rows with no divisor of 4 to 16 groups (G a prime above 16, 34, 51) use
 // 16-group chunks whose last may be shorter.
 // Stores: see pack_policy.  Rows carry no reuse across workgroups, so the
 // workgroup-to-XCD placement needs no remapping.
@@ -141,6 +142,38 @@ __global__ __launch_bounds__(1024) void pack_kernel(const u32x4 *__restrict__ x,
         __threadfence_system();
 }
 
+// One wave per (token, chunk): the chunk is loaded once (non-temporal), before the positions
+// are known, and stored to its token's rows.  Whole groups only (pack_token_waves).
+template <int U, int SP>
+__global__ __launch_bounds__(256) void pack_token_kernel(const u32x4 *__restrict__ x,
+                                                         const int32_t *__restrict__ slot_pos,
+                                                         u32x4 *__restrict__ packed_rows, PackArgs a) {
+    u32x4 *const packed = a.begin(packed_rows);
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t item = blockIdx.x * (blockDim.x / kWave) + wave;
+    const uint32_t t = a.geom.chunks.div(item);
+    if (t >= a.T)
+        return;
+    const int32_t v0 = (int32_t)(item - t * a.geom.chunks.d) * (U * kWave);
+    const u32x4 *src = x + (int64_t)t * a.geom.V + v0 + lane;
+    u32x4 d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        d[u] = __builtin_nontemporal_load(src + u * kWave);
+    const int32_t *sp = slot_pos + (int64_t)t * a.k;
+    for (int32_t j = 0; j < a.k; ++j) {
+        const int64_t p = sp[j];
+        if (p < 0 || p >= a.max_rows)
+            continue;
+        const RowStore<SP> dst(packed + p * a.geom.V + v0, (uint32_t)(a.geom.V - v0) * 16u);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            dst.put(d[u], u * kWave + lane);
+    }
+    if (a.fence_system)
+        __threadfence_system();
+}
+
 struct PackPtrs {
     const u32x4 *x;
     const int32_t *slot_pos;
@@ -149,7 +182,13 @@ struct PackPtrs {
 
 template <int U, int EDGE, int SP>
 void launch_pack_u(dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts, const PackPtrs &p,
-                   const PackArgs &a) {
+                   const PackArgs &a, bool token_waves) {
+    if constexpr (EDGE == kWhole)
+        if (token_waves) {
+            hipExtLaunchKernelGGL((pack_token_kernel<U, SP>), grid, block, 0, stream, ts.start, ts.stop, 0, p.x,
+                                  p.slot_pos, p.packed, a);
+            return;
+        }
     if (a.k == 1)
         hipExtLaunchKernelGGL((pack_kernel<U, EDGE, SP, true>), grid, block, 0, stream, ts.start, ts.stop, 0, p.x,
                               p.slot_pos, p.packed, a);
@@ -163,21 +202,21 @@ constexpr int kMaxU = 16;  // longest chunk: 16 KiB
 // Launches the instance for chunks of `u` whole groups (0: the ragged instance).
 template <int SP, int U = kMaxU>
 void launch_chunk(int u, bool partial, dim3 grid, dim3 block, hipStream_t stream, TraceSlot ts,
-                  const PackPtrs &p, const PackArgs &a) {
+                  const PackPtrs &p, const PackArgs &a, bool token_waves) {
     if (u == 0)
-        return launch_pack_u<kMaxU, kRagged, SP>(grid, block, stream, ts, p, a);
+        return launch_pack_u<kMaxU, kRagged, SP>(grid, block, stream, ts, p, a, token_waves);
     if (u != U) {
         if constexpr (U > 1)
-            launch_chunk<SP, U - 1>(u, partial, grid, block, stream, ts, p, a);
+            launch_chunk<SP, U - 1>(u, partial, grid, block, stream, ts, p, a, token_waves);
         return;
     }
     if (partial)
-        launch_pack_u<U, kPartial, SP>(grid, block, stream, ts, p, a);
+        launch_pack_u<U, kPartial, SP>(grid, block, stream, ts, p, a, token_waves);
     else
-        launch_pack_u<U, kWhole, SP>(grid, block, stream, ts, p, a);
+        launch_pack_u<U, kWhole, SP>(grid, block, stream, ts, p, a, token_waves);
 }
 
-// Store policy of a launch that packs `bytes` bytes of rows of row_bytes, by the time of
+// Store policy of a launch whose slots' rows of row_bytes make up `bytes` bytes, by the time of
 // whole passes (layout, pack, combine), since what a policy leaves in the caches is paid for by
 // the next kernel.  Measured on MI355X, non-temporal / kStoreWT / kStoreWTStream:
 //   rows of whole 64-byte pieces: 52 MiB of 2 KiB rows 33.9 / 38.2 / 33.8 us, 268 MiB of 4 KiB
@@ -189,29 +228,45 @@ void launch_chunk(int u, bool partial, dim3 grid, dim3 block, hipStream_t stream
 //     18.7 / 20.7 / 19.2, 25 MiB of 2064 B rows (4001, top-3) 23.7 / 29.1 / 24.9.  Write-through is
 //     ahead only where a program packs into the same buffers again at once (14.0 against 14.9, 20.9
 //     against 22.5).
+// A window layout packs only some of its slots' rows; there the policies are within 1% of each
+// other (whole passes, non-temporal / kStoreWTStream: 28 MiB of 224 packed 31.0 / 31.0, 256 of 2048
+// MiB 173.1 / 171.1, 448 of 3584 MiB 315.4 / 316.1), so the slots decide there too.
 // Rows to host memory (graph rounds) go non-temporal.
 int pack_policy(int64_t bytes, int64_t row_bytes, bool to_host) {
     return to_host || row_bytes % 64 != 0 || bytes < (128ll << 20) ? kStoreNT : kStoreWTStream;
+}
+
+// Whether a wave takes a token's chunk for all its rows, not for one.  Its loads need not wait
+// for a position, but rows of absent slots are read too, so only where every slot is expected
+// to have a row.  Measured on MI355X, pack and combine of rows in no cache, a wave per token / per
+// slot: top-1 of 12 KiB rows, 2000 tokens 19.6 / 21.0 us (the pack 9.8 / 10.9); top-2 of 12 KiB, 2000
+// tokens 26.6 / 29.6, of 14 KiB, 1000 tokens 16.8 / 18.6; whole passes of top-2: of 12 KiB rows 47 MiB
+// packed 31.0 / 33.8, 117 MiB 73.6 / 65.0, of 8 KiB 94 MiB (pack and combine) 52.4 / 48.2.  In a window of
+// a quarter of the slots the pack alone takes 75 / 42 (top-2) and 29 / 16 us (top-1).
+bool pack_token_waves(int32_t k, int32_t H, int64_t bytes, Slots expect) {
+    return expect != Slots::kSome && H % (8 * kWave) == 0 && (k == 1 || (k == 2 && bytes < (80ll << 20)));
 }
 
 }  // namespace
 
 hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int32_t *slot_pos,
                        void *packed, int64_t max_rows, uint32_t *epoch_word, uint32_t epoch,
-                       hipStream_t stream, RoundSel sel, bool fence_system) {
+                       hipStream_t stream, Slots expect, RoundSel sel, bool fence_system) {
     if (T == 0)
         return hipSuccess;
+    const int64_t bytes = T * k * (int64_t)H * 2;  // of every slot's row
     const int32_t V = H / 8, lead_mask = V % 8 ? 7 : 0, G = (V + lead_mask + kWave - 1) / kWave;
-    const int64_t rows = T * k;  // waves per chunk of a row
     // chunk length: the largest divisor of G, no short chunks for long rows (0: ragged)
     int u = std::min(G, kMaxU);
     while (G % u != 0)
         --u;
     if (u < std::min(G, 4))
         u = 0;
+    const bool token_waves = u != 0 && pack_token_waves(k, H, bytes, expect);  // exact chunks
+    const int32_t slot_waves = token_waves ? 1 : k;                            // per chunk of a token
     // few tokens: shorter chunks, so that the launch keeps about 1024 waves (measured on
     // MI355X, top-2 of 14 KiB rows: 128 tokens 2.8 against 3.8 us, 512 tokens 5.5 against 6.0)
-    for (int v = u - 1; v >= 1 && rows * (G / u) < 1024; --v)
+    for (int v = u - 1; v >= 1 && T * slot_waves * (G / u) < 1024; --v)
         if (G % v == 0)
             u = v;
     PackArgs a;
@@ -231,15 +286,15 @@ hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int
     // (consecutive workgroups run on different XCDs, each with its own L2): a workgroup of k
     // waves holds them all, so the row is fetched from HBM once (4-wave workgroups fetched
     // it twice at k = 8; measured on MI355X)
-    const int waves = k >= 2 && k <= 16 ? k : 4;
-    const int64_t waves_per_token = (int64_t)a.geom.chunks.d * k;
+    const int waves = slot_waves >= 2 && slot_waves <= 16 ? slot_waves : 4;
+    const int64_t waves_per_token = (int64_t)a.geom.chunks.d * slot_waves;
     // launches of at most 2^31 waves (what FastDiv divides); one for any real layer
     const int64_t per = std::min<int64_t>(T, (INT32_MAX - waves) / waves_per_token);
     if (per < 1)
         return hipErrorInvalidValue;
     (void)hipGetLastError();  // drop an error left by an earlier, already reported call
     const TraceSlot ts = trace_acquire();
-    const int policy = pack_policy(T * k * (int64_t)V * 16, V * 16, sel.round != nullptr);
+    const int policy = pack_policy(bytes, V * 16, sel.round != nullptr);
     for (int64_t t0 = 0; t0 < T; t0 += per) {
         a.T = (uint32_t)std::min(per, T - t0);
         const PackPtrs p{static_cast<const u32x4 *>(x) + t0 * V, slot_pos + t0 * k, static_cast<u32x4 *>(packed)};
@@ -248,9 +303,9 @@ hipError_t launch_pack(const void *x, int64_t T, int32_t H, int32_t k, const int
         part.start = t0 == 0 ? ts.start : nullptr;
         part.stop = t0 + a.T == T ? ts.stop : nullptr;
         if (policy == kStoreWTStream)
-            launch_chunk<kStoreWTStream>(u, V % kWave != 0, grid, block, stream, part, p, a);
+            launch_chunk<kStoreWTStream>(u, V % kWave != 0, grid, block, stream, part, p, a, token_waves);
         else
-            launch_chunk<kStoreNT>(u, V % kWave != 0, grid, block, stream, part, p, a);
+            launch_chunk<kStoreNT>(u, V % kWave != 0, grid, block, stream, part, p, a, token_waves);
     }
     const hipError_t err = hipGetLastError();
     if (err == hipSuccess)

@@ -21,8 +21,13 @@ CASES += [(1025, 7176, 3),       # 15 groups, partly filled, enough waves for wh
           (4000, 4128, 4), (4100, 4096, 4)]    # 64-byte and whole-line rows, past 128 MiB packed
 
 
-@pytest.mark.parametrize("T,H,k", CASES)
-def test_pack_rows(T, H, k):
+# through ep_dispatch, where whole rows of top-1 and of top-2 below 80 MiB take a wave per token
+DISPATCH = [(T, H, k) for k in (1, 2, 3) for T, H in ((1, 512), (37, 6144), (1025, 1536), (300, 9216), (65, 17408))]
+DISPATCH += [(3413, 6144, 2), (3414, 6144, 2), (700, 520, 2), (700, 520, 1)]
+
+
+@pytest.mark.parametrize("T,H,k,by", [(*c, "pack") for c in CASES] + [(*c, "dispatch") for c in DISPATCH])
+def test_pack_rows(T, H, k, by):
     gen = torch.Generator(device=DEV).manual_seed(T * 31 + H + k)
     x = torch.randint(-2**15, 2**15, (T, H), device=DEV, dtype=torch.int16, generator=gen)
     rows = T * k
@@ -31,8 +36,15 @@ def test_pack_rows(T, H, k):
     beyond = missing & (torch.arange(rows, device=DEV) % 2 == 0)
     given = torch.where(missing, torch.where(beyond, rows + pos, -1 - pos), pos).to(torch.int32)
     out = torch.full((rows + 1, H), 0x5A5A, dtype=torch.int16, device=DEV)  # a row more than max_rows
-    say(f"pack T={T} H={H} k={k}")
-    ep.pack(x, given, out[:rows], topk=k)
+    say(f"{by} T={T} H={H} k={k}")
+    if by == "pack":
+        ep.pack(x, given, out[:rows], topk=k)
+    else:
+        st = ep.Staging("hbm", rows, H, 1, num_buffers=1)
+        st.write_device("send", out[:rows])
+        ep.dispatch(x, given, st, topk=k)
+        out[:rows] = st.read_device("send", rows)
+        st.close()
     want = torch.full_like(out, 0x5A5A)
     keep = ~missing
     want[pos[keep].long()] = x.repeat_interleave(k, dim=0)[keep]
