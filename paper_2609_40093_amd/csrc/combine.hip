@@ -428,7 +428,11 @@ hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float
     if (T == 0)
         return hipSuccess;
     const CombineCall c{expect, recv, slot_pos, topk_w, T, out_f32 ? H / 4 : H / 8, k, out, max_rows, sel};
-    if (sel.round)  // graph-replayed rounds: the general instance reading the round
+    // Graph-replayed rounds: the general instance reading the round, for every k and row length:
+    // PCIe bounds a round (with an instance per k before / this, compute-unit and SDMA legs: top-8 of
+    // 14 KiB rows, 256 tokens 1178 / 1168 and 1129 / 1128 us, top-2 of 8 KiB, 4096 tokens 2533 / 2536 and
+    // 2563 / 2560, top-2 of 2 KiB, 128 tokens 49.8 / 49.2 and 140 / 140).
+    if (sel.round)
         return out_f32 ? launch_ranges<4, 8, true, false, false, true>(c, stream)
                        : launch_ranges<2, 8, false, false, false, true>(c, stream);
     switch (k) {
@@ -440,7 +444,15 @@ hipError_t launch_combine(const void *recv, const int32_t *slot_pos, const float
     case 6: return launch_k<6, true>(c, H, out_f32, stream);
     case 7: return launch_k<7, true>(c, H, out_f32, stream);
     case 8: return launch_k<8, true>(c, H, out_f32, stream);
-    default: return launch_k<8, false>(c, H, out_f32, stream);
+    default:
+        // Rows that are no whole number of two-unit chunks: two units all the same where that
+        // leaves a wave per SIMD and more.  Measured on MI355X, one-unit / two-unit chunks: top-24, 4001
+        // tokens of 2064 B rows 41.0 / 39.7 us, 2000 of 5776 B 53.3 / 51.5, top-64, 1500 of 5136 B 91.0 /
+        // 88.5, top-16, 1000 of 6000 B 20.1 / 19.7; 500 of 1040 B 4.7 / 5.7, top-96, 500 of 3088 B 25.9 /
+        // 29.6; fp32 results 42.7 / 46.8, 55.8 / 53.8, 93.5 / 93.5.
+        if (!out_f32 && H % 1024 != 0 && H > 512 && H < 6144 && T * ((H + 1023) / 1024) >= 1536)
+            return launch_ranges<2, 8, false, false, false, false>(c, stream);
+        return launch_k<8, false>(c, H, out_f32, stream);
     }
 }
 
