@@ -412,38 +412,38 @@ void launch_one(const FusedArgs &a, int32_t tpw, int32_t split, unsigned blocks,
                           ts.start, ts.stop, 0, a, tpw, split);  // the last workgroup checks the routing
 }
 
+// Launches top-K's instance.  MULTI: whether the limits let these sizes have more ids than one
+// batch of loads covers.
+template <int U, int K, bool MULTI>
+hipError_t launch_top(const FusedArgs &a, int32_t tpw, int32_t split, unsigned blocks, int threads,
+                      hipStream_t stream, TraceSlot ts) {
+    const bool multi = a.T * a.k > (int64_t)threads * kFBatch * 4;  // one batch: kFBatch 4-id groups per thread
+    const bool wide = a.E > kFNarrowE;
+    if (multi && (wide || !MULTI))
+        return hipErrorInvalidValue;  // excluded by the limits
+    if (wide)
+        launch_one<U, K, false, true>(a, tpw, split, blocks, threads, stream, ts);
+    else if (!multi)
+        launch_one<U, K, false, false>(a, tpw, split, blocks, threads, stream, ts);
+    else if constexpr (MULTI)
+        launch_one<U, K, true, false>(a, tpw, split, blocks, threads, stream, ts);
+    return hipSuccess;
+}
+
 // Picks the instance: the count loop only where one batch of loads does not cover every
-// id (never within the wide limits: at most 16384 ids, 1024 threads x 16), four experts
-// per lane above 64 experts.
+// id (1024 threads x 16 ids: never within the limits of more than 64 experts or top-8, nor with
+// so few bytes packed as top-2 may have in rows of 14 groups and top-4 in rows of 8), four
+// experts per lane above 64 experts.
 template <int U>
 hipError_t launch_k(const FusedArgs &a, int32_t tpw, int32_t split, unsigned blocks, int threads, hipStream_t stream,
                     TraceSlot ts) {
-    const bool multi = a.T * a.k > (int64_t)threads * kFBatch * 4;  // one batch: kFBatch 4-id groups per thread
-    const bool wide = a.E > kFNarrowE;
-    if ((wide || a.k == 8) && multi)
-        return hipErrorInvalidValue;  // excluded by the limits
+    static_assert(kFMaxBytesTop2 / (14 * 1024) <= 16384 && kFMaxBytes / (8 * 1024) <= 16384, "see above");
     switch (a.k) {
-    case 1:
-        wide ? launch_one<U, 1, false, true>(a, tpw, split, blocks, threads, stream, ts)
-             : (multi ? launch_one<U, 1, true, false>(a, tpw, split, blocks, threads, stream, ts)
-                      : launch_one<U, 1, false, false>(a, tpw, split, blocks, threads, stream, ts));
-        break;
-    case 2:
-        wide ? launch_one<U, 2, false, true>(a, tpw, split, blocks, threads, stream, ts)
-             : (multi ? launch_one<U, 2, true, false>(a, tpw, split, blocks, threads, stream, ts)
-                      : launch_one<U, 2, false, false>(a, tpw, split, blocks, threads, stream, ts));
-        break;
-    case 4:
-        wide ? launch_one<U, 4, false, true>(a, tpw, split, blocks, threads, stream, ts)
-             : (multi ? launch_one<U, 4, true, false>(a, tpw, split, blocks, threads, stream, ts)
-                      : launch_one<U, 4, false, false>(a, tpw, split, blocks, threads, stream, ts));
-        break;
-    default:
-        wide ? launch_one<U, 8, false, true>(a, tpw, split, blocks, threads, stream, ts)
-             : launch_one<U, 8, false, false>(a, tpw, split, blocks, threads, stream, ts);
-        break;
+    case 1: return launch_top<U, 1, true>(a, tpw, split, blocks, threads, stream, ts);
+    case 2: return launch_top<U, 2, (U < 14)>(a, tpw, split, blocks, threads, stream, ts);
+    case 4: return launch_top<U, 4, (U < 8)>(a, tpw, split, blocks, threads, stream, ts);
+    default: return launch_top<U, 8, false>(a, tpw, split, blocks, threads, stream, ts);
     }
-    return hipSuccess;
 }
 
 // Workgroups of one call.  Below kFSplitBelow tokens a row is split over the fewest waves
