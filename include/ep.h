@@ -497,7 +497,8 @@ ep_status ep_copy_probe(void *dst_dev, const void *src_dev, size_t bytes, hipStr
  * 0..64, not both 0.  src: units*reads*row_bytes bytes (may be NULL when reads == 0);
  * dst: units*writes*row_bytes bytes, or 1 KiB when writes == 0.  store_policy (the path's
  * three): 0 non-temporal 16-byte stores, 1 device-scope write-through buffer stores (the
- * combine below 44 MiB of output), 2 the same with the non-temporal hint (the pack from
+ * combine below 44 MiB of output, 88 MiB after the one-kernel dispatch), 2 the same with the
+ * non-temporal hint (the pack of rows of whole 64-byte pieces from
  * 128 MiB per launch); any other value is EP_ERR_INVALID_ARG.  Traced as "stream_probe". */
 ep_status ep_stream_probe(void *dst_dev, const void *src_dev, int64_t units, int32_t row_bytes, int32_t reads,
                           int32_t writes, int32_t store_policy, hipStream_t stream);

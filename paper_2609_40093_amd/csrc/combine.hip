@@ -21,8 +21,8 @@
 // 31.5 us at 2047 tokens, top-4 of 10 KiB rows to fp32; this: 19.6 us, 6.4 TB/s).
 // In EXACT instances (rows a whole number of chunks) no lane carries a bounds mask.
 // Rows are read once: loads are non-temporal.  Stores are device-scope write-through
-// buffer stores when the output is under kCombineWriteThroughBelow and non-temporal from
-// there up (RowStore); from 128 MiB up the call runs as launches of about 64 MiB of output
+// buffer stores when the output is small (write_through_below) and non-temporal from there
+// up (RowStore); from 128 MiB up the call runs as launches of about 64 MiB of output
 // each (see the launcher).
 #include "ep_internal.h"
 
@@ -211,8 +211,14 @@ constexpr int64_t kCombineSplitAbove = 128ll << 20;
 constexpr int64_t kCombineLaunchBytes = 64ll << 20;
 
 // LDS a workgroup reserves (and does not use) to limit the workgroups per compute unit, so
-// that about 96 to 128 KiB of row loads are in flight on each: a wave has loads_512 * 512
-// bytes in flight.  More waves at once spread the reads over more rows and HBM pages.
+// that 80 to 128 KiB of row loads are in flight on each: a wave has loads_512 * 512 bytes in
+// flight (five slots in one-unit chunks, at most 5 KiB a wave, are not limited).  More waves at
+// once spread the reads over more rows and HBM pages.  A kernel on another stream gets in the
+// sooner for it, though it finds little LDS free, because the waves' slots and registers stay
+// free: beside the combine of 16384 tokens, top-8 of 14 KiB rows (370 us), limited / not, four
+// 512 x 2048 x 4096 products end after 273 / 428 us, a layout after 30 / 96; full-chip products (4096^3)
+// and the combine together take as long either way (1137 / 1138 us; 8 KiB rows 1014 / 1004, top-6 of 8192
+// tokens 531 / 520).
 // Measured on MI355X over whole passes, non-temporal regime, 4-wave workgroups per compute
 // unit (none: as many as fit):
 //   8 loads of 1 KiB (top-8, 14 KiB rows): 32768 tokens, skewed routing none / 4 / 3 / 2 1487 /

@@ -26,7 +26,7 @@
 //   count  one workgroup per tile of the routing array: the tile's histogram and routing
 //          errors (ids outside [0,E), an expert twice in one token row), to the workspace.
 //   rank   several workgroups per tile, each owning a run of it: sums every tile's counts
-//          (a thread per run of tiles of an expert's column, 16 loads in flight), which
+//          (a thread per run of tiles of an expert's column, 8 loads in flight), which
 //          gives the expert totals and the rows of each expert in earlier tiles;
 //          histograms the entries of its tile before its run; scans the totals; ranks its
 //          run and writes every position: expert offset + rows of the expert in earlier
@@ -41,7 +41,7 @@
 // workgroups spread over every compute unit.  Measured on MI355X, layouts back to back,
 // against counting everything with ballots in one 16-wave workgroup per tile: 2048 entries
 // of 256 experts 4.6 us (before 7.2), 8188 of 64 5.2 (8.7), 65536 of 128 8.6 (10.8), 262144
-// of 256 11.3 (17.0), 1M of 256 17.6 (49).
+// of 256 11.3 (17.0), 1M of 256 17.3 (49).
 // Cross-tile traffic: tiles x E words written once, read by every rank workgroup (from L2
 // after its XCD's first miss), and tiles error words read by the first.
 #include "ep_internal.h"
