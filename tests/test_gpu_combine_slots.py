@@ -47,6 +47,40 @@ def test_slots_without_rows(k, H):
         assert not out.view(torch.int32 if dt == torch.float32 else torch.int16).cpu().numpy()[empty].any()
 
 
+@pytest.mark.parametrize("k,H,dtype", [(8, 7168, torch.bfloat16), (6, 6152, torch.bfloat16), (5, 3072, torch.float32),
+                                       (7, 3592, torch.float32), (8, 4096, torch.float32)])
+def test_missing_slots_in_large_outputs(k, H, dtype):
+    """Slots without rows above 44 MiB of output and more than four slots, where a combine of a
+    whole layout also reserves LDS: through ep_combine and ep_combine_rows, the same bits."""
+    T, rows = 4096, 5000
+    gen = torch.Generator(device=DEV).manual_seed(k * H)
+    y = torch.empty((rows, H), device=DEV, dtype=torch.bfloat16).normal_(generator=gen)
+    w = torch.randn((T, k), device=DEV, generator=gen)
+    pos = torch.randint(0, rows, (T, k), device=DEV, generator=gen, dtype=torch.int32)
+    share = torch.tensor([0.0, 0.5, 0.9], device=DEV)[torch.arange(T, device=DEV) % 3]
+    missing = torch.rand((T, k), device=DEV, generator=gen) < share[:, None]
+    pos[missing] = torch.where(torch.rand(int(missing.sum()), device=DEV, generator=gen) < 0.5, -1, T * k + 3).to(torch.int32)
+    assert T * H * (2 if dtype == torch.bfloat16 else 4) > 44 << 20
+    exact = torch.zeros((T, H), dtype=torch.float64, device=DEV)
+    size = torch.zeros_like(exact)
+    for j in range(k):
+        term = torch.where(missing[:, j], 0.0, w[:, j].double())[:, None] * y[pos[:, j].clamp(0, rows - 1).long()].double()
+        exact += term
+        size += term.abs()
+    bound = ((~missing).sum(dim=1)[:, None] + 1) * 2.0**-24 * size
+    if dtype == torch.bfloat16:
+        bound = bound + 2.0**-8 * (exact.abs() + bound)
+    st = ep.Staging("hbm", T * k, H, 1, num_buffers=1)
+    st.write_device("recv", y.view(torch.int16))
+    flat = pos.reshape(-1).contiguous()
+    say(f"combine of {T} tokens with missing slots: k={k} H={H} {dtype}")
+    out = ep.combine(st, flat, w, out=torch.full((T, H), 7.0, dtype=dtype, device=DEV))
+    assert (out.double() - exact).abs().le(bound).all()
+    say("and from the caller's rows")
+    assert torch.equal(ep.combine_rows(y, flat, w, torch.full((T, H), 7.0, dtype=dtype, device=DEV)), out)
+    st.close()
+
+
 @pytest.mark.parametrize("H,dtype", [(7168, torch.bfloat16), (3584, torch.float32)])
 def test_store_policies_agree(H, dtype):
     """The combine stores by its output's bytes and by how its rows were dispatched (one kernel,
