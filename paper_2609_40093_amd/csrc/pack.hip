@@ -225,7 +225,7 @@ void launch_chunk(int u, bool partial, dim3 grid, dim3 block, hipStream_t stream
 //   other rows, whose ends share a cache line with their neighbours': non-temporal at any size.
 //     93 MiB of 8208 B rows 54 / 71 / 62; 875 MiB of 14352 B rows 435 / 520 / 484, 2189 MiB 1069 / 1330
 //     / 1195; 17 MiB of 5776 B rows (500 tokens, top-6) in no cache 16.4 / 18.9 / 16.9, just written
-//     18.7 / 20.7 / 19.2, 25 MiB of 2064 B rows (4001, top-3) 23.7 / 29.1 / 24.9.  Write-through is
+//     18.7 / 20.7 / 19.2, 24 MiB of 2064 B rows (4001, top-3) 23.7 / 29.1 / 24.9.  Write-through is
 //     ahead only where a program packs into the same buffers again at once (14.0 against 14.9, 20.9
 //     against 22.5).
 // A window layout packs only some of its slots' rows; there the policies are within 1% of each
@@ -242,7 +242,8 @@ int pack_policy(int64_t bytes, int64_t row_bytes, bool to_host) {
 // slot: top-1 of 12 KiB rows, 2000 tokens 19.6 / 21.0 us (the pack 9.8 / 10.9); top-2 of 12 KiB, 2000
 // tokens 26.6 / 29.6, of 14 KiB, 1000 tokens 16.8 / 18.6; whole passes of top-2: of 12 KiB rows 47 MiB
 // packed 31.0 / 33.8, 117 MiB 73.6 / 65.0, of 8 KiB 94 MiB (pack and combine) 52.4 / 48.2.  In a window of
-// a quarter of the slots the pack alone takes 75 / 42 (top-2) and 29 / 16 us (top-1).
+// a quarter of the slots the pack alone takes 75 / 42 (top-2, 32768 tokens of 8 KiB rows) and 29 / 16 us
+// (top-1, 16384).
 bool pack_token_waves(int32_t k, int32_t H, int64_t bytes, Slots expect) {
     return expect != Slots::kSome && H % (8 * kWave) == 0 && (k == 1 || (k == 2 && bytes < (80ll << 20)));
 }

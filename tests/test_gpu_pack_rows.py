@@ -17,13 +17,13 @@ CASES += [(1025, 7176, 3),       # 15 groups, partly filled, enough waves for wh
           (300, 8712, 2),        # 18 groups
           (600, 9736, 6),        # 20 groups
           (130, 8640, 4),        # 17 groups: no divisor, chunks of 16 and 1
-          (2500, 2056, 4), (5200, 2056, 4),    # rows of 16-byte ends, below and above 40 MiB packed
-          (4000, 4128, 4), (4100, 4096, 4)]    # 64-byte and whole-line rows, past 128 MiB packed
+          (2500, 2056, 4), (5200, 2056, 4),    # rows of 16-byte ends
+          (4100, 4128, 4), (4100, 4096, 4)]    # 64-byte and whole-line rows, past 128 MiB packed
 
 
 # through ep_dispatch, where whole rows of top-1 and of top-2 below 80 MiB take a wave per token
 DISPATCH = [(T, H, k) for k in (1, 2, 3) for T, H in ((1, 512), (37, 6144), (1025, 1536), (300, 9216), (65, 17408))]
-DISPATCH += [(3413, 6144, 2), (3414, 6144, 2), (700, 520, 2), (700, 520, 1)]
+DISPATCH += [(3413, 6144, 2), (3414, 6144, 2), (700, 520, 2), (700, 520, 1), (11000, 6144, 1)]  # the last: 129 MiB
 
 
 @pytest.mark.parametrize("T,H,k,by", [(*c, "pack") for c in CASES] + [(*c, "dispatch") for c in DISPATCH])
